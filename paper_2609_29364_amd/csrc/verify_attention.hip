@@ -108,7 +108,7 @@ __host__ __device__ constexpr int waves_per_simd(int, int, bool) { return 1; }
 struct CutRec {
   int64_t base;     // span position of the item's first span
   int32_t n;        // the item's spans; -1: the range leaves nothing to merge
-  int32_t r, g, qo, nq, pad;
+  int32_t g, qo, nq;
 };
 
 struct Params {
@@ -127,9 +127,8 @@ struct Params {
   uint16_t* part_o;    // [4 * waves][MT*16][D]: head/tail partial per range, O / sum in bf16
   float2* part_ml;     // [4 * waves][MT*16]: (running max, sum)
   struct CutRec* cut_rec;  // [2 * waves]: the item each range cuts at its end, for the merge
-  uint32_t* prefix;    // [bs+1]: exclusive span prefix over the work order's positions
-  uint32_t* pos_of;    // [bs+1]: position of each request; [bs]: resident requests;
-                       // then [2]: spans of the two segments (per KV head)
+  uint32_t* head;      // [4]: spans (per KV head) of the two segments, waves in use, 0
+  uint2* req;          // [bs]: each request's exclusive span prefix and its spans (per KV head)
   int32_t num_blocks;    // blocks in the worker pool (tiles fit 32-bit indexes)
   int32_t stage_blocks;  // blocks in the staging pool (0 without fusion)
   int32_t bs;
@@ -139,7 +138,8 @@ struct Params {
   int32_t group;
   int32_t max_q;
   int32_t max_seq_len;
-  int32_t num_waves;
+  int32_t num_waves;       // waves of the launch
+  int32_t merge_waves;     // bound of the ranges per segment the waves take, from the longest context
   int32_t out_off;         // dynamic LDS: byte offset of the output buffers
   int32_t out_cap;         // bytes of each wave's output buffer
   int32_t w_even;          // relative range length of waves on even XCDs
@@ -762,12 +762,19 @@ struct Ranges {
   // with weight_before(q) <= G = floor(((s + 1) * total - 1) / T), found by
   // inverting the piecewise-linear weight_before
   __device__ int64_t of(int64_t s) const {
-    const int64_t G = ((s + 1) * total - 1) / T;
-    const int64_t blk = 4 * (we + wo);
-    const int64_t full = G / blk;
-    const int64_t rem = G - full * blk;
-    const int64_t k = rem < 4 * we ? rem / we : 4 + min((int64_t)3, (rem - 4 * we) / wo);
-    return min(W - 1, full * 8 + k);
+    // floor(x / T) by an fp64 quotient: the quotient stays below 2^27 (the
+    // total weight), so it is off by at most one, which the remainder shows
+    // (a 64-bit integer division is over a hundred instructions)
+    const int64_t x = (s + 1) * total - 1;
+    int64_t G = (int64_t)((double)x / (double)T);
+    const int64_t rest = x - G * T;
+    G += rest < 0 ? -1 : (rest >= T ? 1 : 0);
+    const uint32_t blk = (uint32_t)(4 * (we + wo));
+    const uint32_t full = (uint32_t)G / blk;
+    const uint32_t rem = (uint32_t)G - full * blk;
+    const uint32_t e = (uint32_t)we, o = (uint32_t)wo;
+    const uint32_t k = rem < 4 * e ? rem / e : 4 + min(3u, (rem - 4 * e) / o);
+    return min(W - 1, (int64_t)full * 8 + k);
   }
 };
 
@@ -790,12 +797,14 @@ __device__ inline int64_t segment_blocks(int64_t ta, int64_t tb) {
   return ta * span_blocks(D, MT, false) + tb * span_blocks(D, MT, true);
 }
 
-template <int D, int MT, bool FUSE>
-__device__ inline int64_t waves_for(int64_t ta, int64_t tb, int64_t W) {
-  const int64_t B = segment_blocks<D, MT>(ta, tb);
+// Non-decreasing in B (the host bounds the count by the longest context).
+template <bool FUSE>
+__host__ __device__ inline int64_t waves_for(int64_t B, int64_t W) {
   int64_t want = FUSE ? B * 1000 / (15000 + B) : (B + 19) / 20;
   if (FUSE && 8 * want > 7 * W) want = W;
-  return min(W, max((int64_t)kMinWaves, (want + 3) / 4 * 4));
+  want = (want + 3) / 4 * 4;
+  if (want < kMinWaves) want = kMinWaves;
+  return want < W ? want : W;
 }
 
 // Work-order position whose spans [hkv*pre[i], hkv*pre[i+1]) contain span s.
@@ -854,13 +863,11 @@ __device__ inline void run_item(const Params& p, const int32_t* __restrict__ blo
 // The record of range rid for the merge: the item it cuts at its end (if that
 // item began in the range), or none.
 __device__ __attribute__((always_inline)) inline void write_cut_rec(
-    const Params& p, int64_t rid, int lane, bool cut, int64_t base, int n, int r, int g, int qo,
-    int nq) {
+    const Params& p, int64_t rid, int lane, bool cut, int64_t base, int n, int g, int qo, int nq) {
   if (lane != 0) return;
   CutRec* c = p.cut_rec + rid;
   c->base = base;
   c->n = cut ? n : -1;
-  c->r = r;
   c->g = g;
   c->qo = qo;
   c->nq = nq;
@@ -868,7 +875,7 @@ __device__ __attribute__((always_inline)) inline void write_cut_rec(
 
 __device__ __attribute__((always_inline)) inline void write_no_cut(const Params& p, int64_t rid,
                                                                     int lane) {
-  write_cut_rec(p, rid, lane, false, 0, 0, 0, 0, 0, 0);
+  write_cut_rec(p, rid, lane, false, 0, 0, 0, 0, 0);
 }
 
 // One range [s, s1) of global spans, range id rid: online softmax over every
@@ -933,7 +940,7 @@ __device__ void process_range(const Params& p, const int32_t* __restrict__ block
     if (!more) {
       // the range's last item, if it began here and continues past the range
       const bool cut = it.j0 == 0 && it.j1 < it.n && it.rows > 0;
-      write_cut_rec(p, rid, lane, cut, it.base, it.n, it.r, it.g, it.qo, it.nq);
+      write_cut_rec(p, rid, lane, cut, it.base, it.n, it.g, it.qo, it.nq);
       break;
     }
     // switch to the next item (its first span, and Q when reading only, are
@@ -1082,25 +1089,14 @@ void verify_attention_kernel(Params p, const int32_t* __restrict__ block_table,
       const uint32_t pre = arr ? u_res + before[1] + incl[1] - v[1] : before[2] + incl[2] - v[2];
       s_pre[pos] = pre;
       if constexpr (FUSE) s_order[pos] = (uint16_t)r;
-      if (blockIdx.x == 0) {
-        p.prefix[pos] = pre;
-        p.pos_of[r] = pos;
-      }
+      if (blockIdx.x == 0) p.req[r] = make_uint2(pre, n);
     }
     c_arr += s_wsum[0][0] + s_wsum[0][1] + s_wsum[0][2] + s_wsum[0][3];
     c_ua += s_wsum[1][0] + s_wsum[1][1] + s_wsum[1][2] + s_wsum[1][3];
     c_ur += s_wsum[2][0] + s_wsum[2][1] + s_wsum[2][2] + s_wsum[2][3];
     __syncthreads();
   }
-  if (tid == 0) {
-    s_pre[p.bs] = c_ua + c_ur;
-    if (blockIdx.x == 0) {
-      p.prefix[p.bs] = c_ua + c_ur;
-      p.pos_of[p.bs] = n_res;
-      p.pos_of[p.bs + 1] = c_ur;   // spans of the resident segment, per KV head
-      p.pos_of[p.bs + 2] = c_ua;   // of the arriving segment
-    }
-  }
+  if (tid == 0) s_pre[p.bs] = c_ua + c_ur;
   __syncthreads();
 
   const int64_t hkv = p.num_kv_heads;
@@ -1115,7 +1111,9 @@ void verify_attention_kernel(Params p, const int32_t* __restrict__ block_table,
                           p.num_waves, lane);
     return;
   }
-  const int64_t W = waves_for<D, MT, FUSE>(ta, tb, p.num_waves);
+  const int64_t W = waves_for<FUSE>(segment_blocks<D, MT>(ta, tb), p.num_waves);
+  if (blockIdx.x == 0 && tid == 0)
+    *(uint4*)p.head = make_uint4(s_pre[n_res], s_pre[p.bs] - s_pre[n_res], (uint32_t)W, 0u);
   // a batch too small for every resident wave: the surplus waves write the
   // staged blocks to the worker pool, so the attention waves stream without
   // stores, when there are enough of them and the batch is small enough for
@@ -1161,127 +1159,158 @@ void verify_attention_kernel(Params p, const int32_t* __restrict__ block_table,
   out_flush<D, MT>(p, ob, lane);
 }
 
-// Threads per row of the merge kernel's 256: a power of two dividing the
-// row's float4 count, with every row of a 16-row-tile item covered.
-__host__ __device__ constexpr int merge_threads_per_row(int vec, int rows) {
-  int t = 1;
-  while (t * 2 <= 256 / rows && t * 2 <= vec) t *= 2;
-  return t;
+// One wave's running merge of partial rows: a lane holds 8 columns of one row.
+struct MergeAcc {
+  float m, l;
+  float o[8];
+};
+
+__device__ inline void merge_init(MergeAcc& a) {
+  a.m = -INFINITY;
+  a.l = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a.o[i] = 0.f;
 }
 
+// Merge `a` (unnormalised: weights sum to l) with o scaled by w = 2^(m - max) * scale.
+__device__ inline void merge_into(MergeAcc& a, float m, float l, float scale,
+                                  const float (&o)[8]) {
+  if (m == -INFINITY) return;   // no visible token in that part
+  const float mx = fmaxf(a.m, m);
+  const float x = a.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(a.m - mx);
+  const float y = __builtin_amdgcn_exp2f(m - mx);
+  const float w = y * scale;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a.o[i] = x * a.o[i] + w * o[i];
+  a.l = x * a.l + y * l;
+  a.m = mx;
+}
+
+constexpr int kMergeMaxSplit = 16;   // waves that share the parts of one row group
+
 // Merge the partials of every item that a range boundary cut, in range order
-// (deterministic, no atomics).  One workgroup per range (of each segment):
-// it finishes the item the range cuts at its end, if that item began in the
-// range, from the range's record; the ranges holding the item's other parts
-// and their partial slots are found once per workgroup.
-template <int D, int MT, bool FUSE>
-__global__ __launch_bounds__(256) void combine_kernel(Params p) {
-  __shared__ int64_t s_slot[256];   // partial slots of the item, in range order
-  __shared__ int s_nslot;
-  const int x = blockIdx.x;
-  const int tid = threadIdx.x;
-  const bool seg_b = x >= p.num_waves;
-  const int64_t q = seg_b ? x - p.num_waves : x;
+// (deterministic, no atomics).  A wave owns a group of 64 / (D / 8) rows, a
+// lane 8 columns of a row (one 16-byte load per part).
+//
+// BY_ITEM: one workgroup per (item, row group); its waves take the item's
+// parts in turn and their merges meet in LDS.  Used where the items are so
+// few that each is cut into several parts: an item's parts are then read in
+// parallel and its row groups go to different CUs.  Otherwise one workgroup
+// per range (of each segment), a wave per row group: it finishes the item the
+// range cuts at its end, if that item began in the range, from the range's
+// record.  Latency is the bound of both: the launch, one round of loads that
+// says which item it is, one that brings the parts.  Against one workgroup
+// per range that walked an item's parts two at a time: a single request of
+// 32001 tokens (8 items of about 100 parts) 53.1 -> 8.1 us, 24 requests of
+// 1000-4000 tokens (32/8 heads) 11.2 -> 6.0 us, the fused pass of 32 requests
+// 12.5 -> 6.2 us; by range, the fused verify_8b pass 11.8 -> 9.3 us and the
+// 512-request decode 6.7 -> 4.7 us.
+template <int D, int MT, bool BY_ITEM>
+__global__ __launch_bounds__(1024) void combine_kernel(Params p) {
+  constexpr int kLanes = D / 8;            // lanes per row
+  constexpr int kRows = 64 / kLanes;       // rows per wave
+  const int lane = threadIdx.x & 63;
+  const int wave = uniform(threadIdx.x >> 6);
+  const int waves = blockDim.x >> 6;
   const int hkv = p.num_kv_heads;
-  // all independent loads: the row count, the batch's spans, the record
+  // all independent loads: the row count, the batch's spans, the item
   const int total_q = p.q_indptr[p.bs];
-  const int64_t ta = (int64_t)hkv * p.pos_of[p.bs + 1];
-  const int64_t tb = (int64_t)hkv * p.pos_of[p.bs + 2];
-  const CutRec rec = p.cut_rec[x];
-  if (total_q <= 0) return;   // the main kernel attended nothing and wrote no record
-  const int64_t W = waves_for<D, MT, FUSE>(ta, tb, p.num_waves);
-  if (q >= W) return;         // no wave took this range: its record is stale
-  if (rec.n < 0 || rec.nq <= 0) return;
-  const int64_t off = seg_b ? ta : 0;
+  const uint4 head = *(const uint4*)p.head;
+  int64_t base, ra;
+  int n, g, qo, nq;
+  bool seg_b;
+  if constexpr (BY_ITEM) {
+    const int r = blockIdx.x / hkv;
+    g = blockIdx.x - r * hkv;
+    const uint2 rq = p.req[r];
+    n = (int)rq.y;
+    q_rows(p.q_indptr, r, total_q, p.max_q, qo, nq);
+    base = (int64_t)hkv * rq.x + (int64_t)g * n;
+    seg_b = rq.x >= head.x;
+  } else {
+    seg_b = blockIdx.x >= p.merge_waves;
+    ra = seg_b ? blockIdx.x - p.merge_waves : blockIdx.x;
+    const CutRec rec = p.cut_rec[ra + (seg_b ? p.num_waves : 0)];
+    // no wave took this range (its record is stale), or it leaves nothing
+    if (ra >= head.z || rec.n < 0) return;
+    n = rec.n;
+    g = rec.g;
+    qo = rec.qo;
+    nq = min(rec.nq, max(0, total_q - qo));
+    base = rec.base;
+  }
+  if (total_q <= 0 || nq <= 0) return;   // (the main kernel attended nothing and wrote nothing)
+  const int64_t T = (int64_t)hkv * (seg_b ? head.y : head.x), W = head.z;
   const int64_t qoff = seg_b ? p.num_waves : 0;
-  const Ranges R(seg_b ? tb : ta, W, p.w_even, seg_b ? p.w_odd_b : p.w_odd);
-  const int n = rec.n, g = rec.g, qo = rec.qo;
-  const int nq = min(rec.nq, max(0, total_q - qo));
-  const int64_t base = rec.base;
-  const int64_t ra = q;                                      // the item began in this range
-  const int64_t rb = uniform64(R.of(base - off + n - 1));   // its last span's range
-  if (rb <= ra || nq == 0) return;
+  const Ranges R(T, W, p.w_even, seg_b ? p.w_odd_b : p.w_odd);
+  if (seg_b) base -= (int64_t)hkv * head.x;
+  if constexpr (BY_ITEM) ra = R.of(base);
+  const int64_t rb = R.of(base + n - 1);
+  if (rb <= ra) return;                  // one range holds the whole item
   const int rows = p.group * nq;
-  // thread layout: kTPR threads per row, each holding kPer float4 elements of
-  // it (lane-contiguous per element index), so a thread reads one (max, sum)
-  // per part; few registers, so every range's workgroup is resident at once
-  constexpr int kVec = D / 4;
-  constexpr int kTPR = merge_threads_per_row(kVec, MT * 16);
-  constexpr int kPer = kVec / kTPR;
-  const int m = tid / kTPR;                 // this thread's row (idle when >= rows)
-  const int c = tid % kTPR;
-  const int mld = min(m, rows - 1);         // loads clamped into the item's rows
-  float mrun = -INFINITY, drun = 0.f;
-  f32x4 orun[kPer];
+  const int m0 = (BY_ITEM ? (int)blockIdx.y : wave) * kRows;
+  if (m0 >= rows) return;                // (uniform over the workgroup when BY_ITEM)
+  const int split = BY_ITEM ? waves : 1, s0 = BY_ITEM ? wave : 0;
+  const int m = m0 + lane / kLanes, c = lane % kLanes;
+  const int mld = min(m, rows - 1);      // loads clamped into the item's rows
+  // ranges without a span exist only where spans are as few as waves
+  const bool sparse = T < 2 * W;
+  MergeAcc acc;
+  merge_init(acc);
+  constexpr int kAhead = 4;              // parts loaded before the first is merged
+  for (int64_t q0 = ra + s0; q0 <= rb; q0 += (int64_t)split * kAhead) {
+    float2 ml[kAhead];
+    u32x4 w[kAhead];
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) orun[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // running merge over the ranges, 256 at a time (an item rarely spans more
-  // than a few)
-  for (int64_t q0 = ra; q0 <= rb; q0 += 256) {
-    const int64_t q = q0 + tid;
-    if (q <= rb) {
-      int j0, j1;
-      spans_in(base, n, off + R.begin(q), off + R.end(q), j0, j1);
-      s_slot[tid] = j0 < j1 ? 2 * (qoff + q) + (j0 > 0 ? 0 : 1) : -1;
+    for (int u = 0; u < kAhead; ++u) {
+      const int64_t q = min(rb, q0 + (int64_t)u * split);
+      const int64_t row = (2 * (qoff + q) + (q > ra ? 0 : 1)) * (MT * 16) + mld;
+      ml[u] = p.part_ml[row];
+      w[u] = *(const u32x4*)(p.part_o + row * D + c * 8);
     }
-    __syncthreads();
-    if (tid == 0) {   // keep the ranges holding a part, in order
-      const int span = (int)min((int64_t)256, rb - q0 + 1);
-      int n = 0;
-      for (int k = 0; k < span; ++k)
-        if (s_slot[k] >= 0) s_slot[n++] = s_slot[k];
-      s_nslot = n;
-    }
-    __syncthreads();
-    const int cnt = s_nslot;
-    // two parts at a time (a cut item has two in most cases): every load is
-    // issued before the first merge
-    for (int k0 = 0; k0 < cnt; k0 += 2) {
-      float2 ml[2];
-      f32x4 o[2][kPer];
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int64_t slot = s_slot[min(k0 + u, cnt - 1)];
-        const int64_t row = slot * (MT * 16) + mld;
-        ml[u] = p.part_ml[row];
-        const u32x2* src = (const u32x2*)(p.part_o + row * D) + c;
+    for (int u = 0; u < kAhead; ++u) {
+      const int64_t q = q0 + (int64_t)u * split;
+      if (q > rb || (sparse && R.begin(q) >= R.end(q))) continue;
+      // bf16 to fp32 by placing each half in the high bits (exact)
+      float o[8];
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-          // bf16 to fp32 by placing each half in the high bits (exact); the
-          // compiler's conversion of bf16 vector elements read the low word
-          // for both halves here
-          const u32x2 w = src[i * kTPR];
-          o[u][i] = f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u),
-                          __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xffff0000u)};
-        }
+      for (int i = 0; i < 4; ++i) {
+        o[2 * i] = __uint_as_float(w[u][i] << 16);
+        o[2 * i + 1] = __uint_as_float(w[u][i] & 0xffff0000u);
       }
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        if (k0 + u >= cnt || ml[u].x == -INFINITY) continue;   // no visible token there
-        const float mx = fmaxf(mrun, ml[u].x);
-        const float a = mrun == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrun - mx);
-        const float b = __builtin_amdgcn_exp2f(ml[u].x - mx);
-        const float bl = b * ml[u].y;   // the part's weight: its rows are O / sum
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) orun[i] = a * orun[i] + bl * o[u][i];
-        drun = a * drun + bl;
-        mrun = mx;
-      }
+      merge_into(acc, ml[u].x, ml[u].y, ml[u].y, o);   // the part's rows are O / sum
     }
+  }
+  if constexpr (BY_ITEM) {
+    // the waves' merges meet in LDS, in wave order
+    extern __shared__ float s_part[];      // [waves][10][64]
+    float* mine = s_part + wave * 640 + lane;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mine[i * 64] = acc.o[i];
+    mine[512] = acc.m;
+    mine[576] = acc.l;
     __syncthreads();
+    if (wave != 0) return;
+    for (int k = 1; k < waves; ++k) {
+      const float* from = s_part + k * 640 + lane;
+      float o[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) o[i] = from[i * 64];
+      merge_into(acc, from[512], from[576], 1.f, o);
+    }
   }
   if (m >= rows) return;
-  const float inv = drun > 0.f ? 1.f / drun : 0.f;
+  const float inv = acc.l > 0.f ? 1.f / acc.l : 0.f;
   const int j = m / p.group;
   const int h = g * p.group + m % p.group;
-  uint16_t* dst = p.out + ((int64_t)(qo + j) * p.num_q_heads + h) * D;
+  u32x4 w;
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    const bf16x2 lo = {(__bf16)(orun[i][0] * inv), (__bf16)(orun[i][1] * inv)};
-    const bf16x2 hi = {(__bf16)(orun[i][2] * inv), (__bf16)(orun[i][3] * inv)};
-    *(u32x2*)(dst + (i * kTPR + c) * 4) =
-        u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+  for (int i = 0; i < 4; ++i) {
+    const bf16x2 v = {(__bf16)(acc.o[2 * i] * inv), (__bf16)(acc.o[2 * i + 1] * inv)};
+    w[i] = __builtin_bit_cast(uint32_t, v);
   }
+  *(u32x4*)(p.out + ((int64_t)(qo + j) * p.num_q_heads + h) * D + c * 8) = w;
 }
 
 template <int D, int MT, bool FUSE>
@@ -1412,7 +1441,7 @@ bool make_plan(int bs, int hq, int hkv, int d, int max_q, int max_seq_len, bool 
   pl->num_waves = resident_waves(d, pl->mt, fuse, (pl->lds_bytes + 15) / 16 * 16);
   // a head and a tail slot per range, W ranges in each of the two segments
   const size_t slots = 4 * (size_t)pl->num_waves * pl->mt * 16;
-  pl->prefix_bytes = ((2 * ((size_t)bs + 1) + 2) * sizeof(uint32_t) + 255) / 256 * 256;
+  pl->prefix_bytes = (16 + (size_t)bs * sizeof(uint2) + 255) / 256 * 256;
   pl->part_o_bytes = slots * d * sizeof(uint16_t);
   pl->part_ml_bytes = slots * sizeof(float2);
   pl->cut_rec_bytes = 2 * (size_t)pl->num_waves * sizeof(CutRec);
@@ -1425,9 +1454,23 @@ void launch(const Params& p, int bs, size_t lds_bytes, hipStream_t stream) {
   hipLaunchKernelGGL((verify_attention_kernel<D, MT, FUSE>), dim3(p.num_waves / 4), dim3(256),
                      lds_bytes, stream, p, p.block_table, p.stage_table, p.seq_lens,
                      p.q_indptr);
-  hipLaunchKernelGGL((combine_kernel<D, MT, FUSE>), dim3((FUSE ? 2 : 1) * p.num_waves),
-                     dim3(256), 0, stream, p);
-  (void)bs;
+  // the merge: by item where the ranges are at least twice the items (every
+  // item is cut, so every workgroup has work: 24 requests x 8 KV heads 6.0 us
+  // by item, 7.3 us by range; 32 requests fused 6.2 against 8.4 us), with about one wave for every two parts of an
+  // item; by range otherwise (most items of a large batch are whole: 2048
+  // workgroups by range, not 4096 by item and row group)
+  const int64_t ranges = (int64_t)(FUSE ? 2 : 1) * p.merge_waves;
+  const int64_t items = (int64_t)bs * p.num_kv_heads;
+  const int groups = (p.group * p.max_q + 64 / (D / 8) - 1) / (64 / (D / 8));
+  if (2 * items <= ranges) {
+    int split = 1;
+    while (split < kMergeMaxSplit && 4 * items * split <= ranges) split *= 2;
+    hipLaunchKernelGGL((combine_kernel<D, MT, true>), dim3((uint32_t)items, groups),
+                       dim3(64 * split), (size_t)split * 640 * sizeof(float), stream, p);
+  } else {
+    hipLaunchKernelGGL((combine_kernel<D, MT, false>), dim3((uint32_t)ranges), dim3(64 * groups),
+                       0, stream, p);
+  }
 }
 
 template <int D, bool FUSE>
@@ -1508,8 +1551,8 @@ nsd_status run(const char* fn, bool fuse, const void* q, const void* k_cache,
   p.q_indptr = q_indptr;
   p.out = (uint16_t*)out;
   char* ws = (char*)workspace;
-  p.prefix = (uint32_t*)ws;
-  p.pos_of = p.prefix + bs + 1;
+  p.head = (uint32_t*)ws;
+  p.req = (uint2*)(ws + 16);
   p.part_o = (uint16_t*)(ws + pl.prefix_bytes);
   p.part_ml = (float2*)(ws + pl.prefix_bytes + pl.part_o_bytes);
   p.cut_rec = (CutRec*)(ws + pl.prefix_bytes + pl.part_o_bytes + pl.part_ml_bytes);
@@ -1522,7 +1565,14 @@ nsd_status run(const char* fn, bool fuse, const void* q, const void* k_cache,
   p.group = num_q_heads / num_kv_heads;
   p.max_q = max_q_per_seq;
   p.max_seq_len = max_seq_len;
-  p.num_waves = pl.num_waves;
+  // the most blocks the batch can hold (whole four-block spans, at least one
+  // per item) bound the waves its split uses; without fusion no other wave has
+  // work, so none is launched
+  const int64_t most = std::min<int64_t>(max_seq_len, (int64_t)max_blocks_per_seq * kBlock);
+  const int64_t blocks = (int64_t)bs * num_kv_heads * std::max<int64_t>(1, (most + 63) / 64) * 4;
+  p.merge_waves = (int32_t)(fuse ? waves_for<true>(blocks, pl.num_waves)
+                                 : waves_for<false>(blocks, pl.num_waves));
+  p.num_waves = fuse ? pl.num_waves : p.merge_waves;
   // measured HBM streaming speed of odd-XCD waves relative to even ones, in
   // the read-only resident segment and in the arriving segment (which also
   // writes, widening the gap)
