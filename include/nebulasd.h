@@ -150,8 +150,9 @@ int32_t    nsd_attention_waves(void);
  * of its request.  Query head h reads KV head h / (num_q_heads/num_kv_heads).
  *     out[q_indptr[r]+j][h] = softmax_t(scale * <q, k_t>) . v_t
  * computed from bf16 inputs with fp32 accumulation (the softmax weights enter
- * the second product as bf16; a row split over several waves is merged from
- * per-part rows stored normalised in bf16 with fp32 max and sum); out is
+ * the second product as bf16; a row split over several waves is merged in
+ * fp32, or from per-part rows stored normalised in bf16 with fp32 max and
+ * sum); out is
  * rounded to bf16.
  * A query row with no visible token (only if n_q > L_r) is written as 0.
  *

@@ -57,6 +57,11 @@
 //   partial) go to the wave's LDS buffer, which is written out, in whole
 //   rows, when it is full and when the wave's work ends.  (The fused
 //   variant's own tile stores are the preparation itself and stay in line.)
+// * Short contexts and small batches take another kernel (item_split says
+//   which): a workgroup per (request, KV head), its four waves sharing the
+//   item's spans and merging in LDS, so the call is one launch without a
+//   prologue over the batch; a batch too small to fill the CUs cuts its long
+//   items into chunks of equal length, merged by a second launch.
 // * Masked tokens (past a query's position, past L_r, or in a block whose id
 //   is out of range) are removed by selection: scores become -inf and V
 //   elements past L_r are zeroed, so NaN-filled unused slots never leak.
@@ -67,6 +72,7 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 namespace {
 
@@ -139,6 +145,8 @@ struct Params {
   int32_t max_q;
   int32_t max_seq_len;
   int32_t num_waves;       // waves of the launch
+  int32_t split;           // item kernel: most chunks an item is cut into (1: none is cut)
+  int32_t split_groups;    // item kernel: workgroups the cut aims at
   int32_t merge_waves;     // bound of the ranges per segment the waves take, from the longest context
   int32_t out_off;         // dynamic LDS: byte offset of the output buffers
   int32_t out_cap;         // bytes of each wave's output buffer
@@ -160,6 +168,14 @@ struct VOps {
 template <int MT, int D>
 struct QOps {
   u32x4 q[MT][D / 32];  // Q operands of one item (fetched one item ahead)
+  __device__ u32x4 get(int mt, int kk) const { return q[mt][kk]; }
+};
+
+// Q operands a workgroup's waves share, in LDS: [MT][D/32][64 lanes].
+template <int MT, int D>
+struct QShared {
+  const u32x4* base;    // this lane's first operand
+  __device__ u32x4 get(int mt, int kk) const { return base[(mt * (D / 32) + kk) * 64]; }
 };
 
 // Values every lane of a wave agrees on, marked so for the compiler (uniform
@@ -434,18 +450,22 @@ __device__ inline void store_v(const VOps<D, NB>& o, const Params& p, const Span
 // unconditional): the tile products never mix rows (a row's scores, softmax
 // and output column depend on that row's Q alone), and such rows are never
 // stored, so they need no masking.
+template <int D>
+__device__ inline const uint16_t* q_row(const Params& p, const Item& it, int total_q, int m) {
+  const int mm = min(m, max(it.rows - 1, 0));
+  const int j = mm / p.group;
+  const int h = it.g * p.group + mm % p.group;
+  const int qrow = min(it.qo + j, total_q - 1);
+  return p.q + ((int64_t)qrow * p.num_q_heads + h) * D;
+}
+
 template <int D, int MT>
 __device__ inline void load_q(QOps<MT, D>& o, const Params& p, const Item& it, int total_q,
                               int lane) {
   const int grp = lane >> 4;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
-    const int m = mt * 16 + (lane & 15);
-    const int mm = min(m, max(it.rows - 1, 0));
-    const int j = mm / p.group;
-    const int h = it.g * p.group + mm % p.group;
-    const int qrow = min(it.qo + j, total_q - 1);
-    const uint16_t* src = p.q + ((int64_t)qrow * p.num_q_heads + h) * D;
+    const uint16_t* src = q_row<D>(p, it, total_q, mt * 16 + (lane & 15));
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) o.q[mt][kk] = *(const u32x4*)(src + kk * 32 + grp * 8);
   }
@@ -453,8 +473,8 @@ __device__ inline void load_q(QOps<MT, D>& o, const Params& p, const Item& it, i
 
 // S^T[token][row] of the span's NB blocks; the item's Q operands stay in
 // registers.
-template <int D, int MT, int NB>
-__device__ inline void span_scores(const KOps<D, NB>& k, const QOps<MT, D>& q,
+template <int D, int MT, int NB, class Q>
+__device__ inline void span_scores(const KOps<D, NB>& k, const Q& q,
                                    f32x4 (&st)[NB][MT]) {
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
@@ -463,7 +483,7 @@ __device__ inline void span_scores(const KOps<D, NB>& k, const QOps<MT, D>& q,
     for (int b = 0; b < NB; ++b) c[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) {
-      const bf16x8 qo = __builtin_bit_cast(bf16x8, q.q[mt][kk]);
+      const bf16x8 qo = __builtin_bit_cast(bf16x8, q.get(mt, kk));
 #pragma unroll
       for (int b = 0; b < NB; ++b)
         c[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k.k[b][kk]),
@@ -583,11 +603,12 @@ __device__ inline void span_pv(const VOps<D, NB>& v, const SpanRef<NB>& s, int L
 // the next item) the Q registers, free once the scores are formed, are
 // refilled with nit's Q before its first K/V loads are issued: the loads
 // complete in order, so waiting for that K also covers Q, and the switch to
-// the next item waits for nothing.
-template <int D, int MT, int NB, bool ARR, bool STORE, bool NEXTQ>
+// the next item waits for nothing.  Without FETCH nothing follows this span.
+template <int D, int MT, int NB, bool ARR, bool STORE, bool NEXTQ, bool FETCH = true,
+          class Q>
 __device__ inline void span_step(KOps<D, NB>& kr, VOps<D, NB>& vr, SpanRef<NB>& cur,
                                  const Item& nit, int nj, const SpanIds<NB>& nids,
-                                 QOps<MT, D>& q, const Params& p, Acc<D, MT>& a, int win, int L,
+                                 Q& q, const Params& p, Acc<D, MT>& a, int win, int L,
                                  int total_q, int lane) {
   f32x4 st[NB][MT];
   span_scores<D, MT, NB>(kr, q, st);
@@ -596,14 +617,19 @@ __device__ inline void span_step(KOps<D, NB>& kr, VOps<D, NB>& vr, SpanRef<NB>& 
   // entries) behind the score products
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (NEXTQ) load_q<D, MT>(q, p, nit, total_q, lane);
-  const SpanRef<NB> nr = make_ref<NB, ARR>(p, nit, nj, nids);
-  load_k<D, NB>(kr, nr, lane);
+  SpanRef<NB> nr;
+  if constexpr (FETCH) {
+    nr = make_ref<NB, ARR>(p, nit, nj, nids);
+    load_k<D, NB>(kr, nr, lane);
+  }
   bf16x8 pop[NB / 2][MT];
   span_softmax<D, MT, NB>(st, cur, a, win, p.scale_log2, lane, pop);
   span_pv<D, MT, NB>(vr, cur, L, pop, a, lane);
   if constexpr (STORE) store_v<D, NB>(vr, p, cur, lane);
-  load_v<D, NB>(vr, nr, lane);
-  cur = nr;
+  if constexpr (FETCH) {
+    load_v<D, NB>(vr, nr, lane);
+    cur = nr;
+  }
 }
 
 template <int D, int MT>
@@ -800,7 +826,7 @@ __device__ inline int64_t segment_blocks(int64_t ta, int64_t tb) {
 // Non-decreasing in B (the host bounds the count by the longest context).
 template <bool FUSE>
 __host__ __device__ inline int64_t waves_for(int64_t B, int64_t W) {
-  int64_t want = FUSE ? B * 1000 / (15000 + B) : (B + 19) / 20;
+  int64_t want = FUSE ? B * 1000 / (15000 + B) : (B + 7) / 8;
   if (FUSE && 8 * want > 7 * W) want = W;
   want = (want + 3) / 4 * 4;
   if (want < kMinWaves) want = kMinWaves;
@@ -1159,6 +1185,215 @@ void verify_attention_kernel(Params p, const int32_t* __restrict__ block_table,
   out_flush<D, MT>(p, ob, lane);
 }
 
+// Short contexts and small batches: one workgroup per (request, KV head,
+// chunk), its waves sharing the chunk's spans and merging in LDS in fp32.
+// What bounds it is latency: the chain length, table entry, K/V, merge, paid
+// once per workgroup and hidden only behind other workgroups, so the steps
+// are small (two blocks: registers for two waves per SIMD) and nothing over
+// the batch precedes them.  A whole item is one launch: 4 requests of 64-256
+// tokens (4/2 heads, D 64) 12.5 -> 4.7 us, 32 requests of 64-512 (32/8, D 128,
+// K = 4) 32 -> 11.8 us, the same batch fused 41 -> 11 us.
+constexpr int kItemBlocks = 2;   // blocks per step
+
+// Waves per SIMD the item kernel is compiled for: two where its registers fit
+// 256 (the accumulators then stay in the VGPRs the softmax scales them in,
+// and one workgroup's start and end hide behind another's stream).  With 48
+// rows of head_dim 128 they fit if Q stays in LDS; there that costs less than
+// it gives (2048 items of 64-256 tokens 75 -> 54 us), while the smaller tiles
+// only pay its round trip (about 1 us of 4 to 12) and 64 rows would spill.
+__host__ __device__ constexpr bool item_shares_q(int d, int mt) { return d * mt == 384; }
+
+__host__ __device__ constexpr int item_waves_per_simd(int d, int mt) {
+  return d * mt <= 384 ? 2 : 1;
+}
+
+constexpr int kItemWaves = 4;
+constexpr int kItemStep = kItemBlocks * kBlock * kItemWaves;   // tokens one step of a workgroup takes
+
+// Tokens per chunk: items longer than this are cut (never where p.split is
+// 1).  The batch's tokens over the workgroups the launch aims at, but no more
+// than p.split chunks for the longest context, in whole workgroup steps.
+__device__ inline int chunk_tokens(const Params& p, const int32_t* __restrict__ seq_lens,
+                                   int lane) {
+  if (p.split <= 1) return 0x7fffffff;
+  int64_t sum = 0;
+  int mx = 1;
+  for (int r = lane; r < p.bs; r += 64) {
+    const int L = clamp_len(p, seq_lens, r);
+    sum += L;
+    mx = max(mx, L);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    sum += __shfl_xor(sum, o);
+    mx = max(mx, __shfl_xor(mx, o));
+  }
+  const int64_t share = (sum * p.num_kv_heads + p.split_groups - 1) / p.split_groups;
+  const int64_t c = max(share, (int64_t)((mx + p.split - 1) / p.split));
+  return uniform((int)((c + kItemStep - 1) / kItemStep * kItemStep));
+}
+
+// The item's Q operands into LDS, by the workgroup's waves.
+template <int D, int MT>
+__device__ inline void load_q(QShared<MT, D>& q, const Params& p, const Item& it, int total_q,
+                              u32x4* s_q, int wave, int lane) {
+  q.base = s_q + lane;
+#pragma unroll
+  for (int i0 = 0; i0 < MT * (D / 32); i0 += kItemWaves) {
+    const int i = i0 + wave;      // operand (row tile, k-step)
+    if (i < MT * (D / 32))
+      s_q[i * 64 + lane] =
+          *(const u32x4*)(q_row<D>(p, it, total_q, i / (D / 32) * 16 + (lane & 15)) +
+                          i % (D / 32) * 32 + (lane >> 4) * 8);
+  }
+  __syncthreads();
+}
+
+// The spans [j0, j1) (j0 < j1) of an item by one wave, into a.  The first
+// span's loads are issued before Q is waited for.
+template <int D, int MT, bool ARR>
+__device__ inline void item_spans(const Params& p, const int32_t* __restrict__ block_table,
+                                  const int32_t* __restrict__ stage_table, const Item& it,
+                                  int total_q, Acc<D, MT>& a, u32x4* s_q, int wave, int lane) {
+  constexpr int NB = kItemBlocks;
+  constexpr bool kShared = item_shares_q(D, MT);
+  std::conditional_t<kShared, QShared<MT, D>, QOps<MT, D>> q;
+  const bool any = it.j0 < it.j1;
+  if (!kShared && !any) return;
+  SpanRef<NB> cur =
+      make_ref<NB, ARR>(p, it, it.j0, load_ids<NB, ARR>(p, block_table, stage_table, it, it.j0));
+  KOps<D, NB> k;
+  VOps<D, NB> v;
+  if constexpr (!kShared) load_q<D, MT>(q, p, it, total_q, lane);
+  load_k<D, NB>(k, cur, lane);
+  load_v<D, NB>(v, cur, lane);
+  // every wave takes part (with its last span's loads in hand where it has none)
+  if constexpr (kShared) load_q<D, MT>(q, p, it, total_q, s_q, wave, lane);
+  if (!any) return;
+  SpanIds<NB> ids =
+      load_ids<NB, ARR>(p, block_table, stage_table, it, min(it.j0 + 1, it.j1 - 1));
+  int j = it.j0;
+  if (j + 1 < it.j1) {
+    do {
+      if constexpr (kShared)
+        asm volatile("" ::: "memory");   // Q is read from LDS in every step, not kept
+      const SpanIds<NB> ids2 =
+          load_ids<NB, ARR>(p, block_table, stage_table, it, min(j + 2, it.j1 - 1));
+      span_step<D, MT, NB, ARR, ARR, false>(k, v, cur, it, j + 1, ids, q, p, a, it.win, it.L,
+                                            total_q, lane);
+      ids = ids2;
+    } while (++j + 1 < it.j1);
+  }
+  span_step<D, MT, NB, ARR, ARR, false, false>(k, v, cur, it, it.j1 - 1, ids, q, p, a, it.win,
+                                               it.L, total_q, lane);
+}
+
+template <int D, int MT, bool FUSE>
+__global__ __launch_bounds__(kItemWaves * 64)
+__attribute__((amdgpu_waves_per_eu(item_waves_per_simd(D, MT)))) void
+item_attention_kernel(Params p, const int32_t* __restrict__ block_table,
+                      const int32_t* __restrict__ stage_table,
+                      const int32_t* __restrict__ seq_lens,
+                      const int32_t* __restrict__ q_indptr) {
+  constexpr int NB = kItemBlocks, NW = kItemWaves;
+  constexpr int kPad = D + 4;   // floats per row in LDS: the rows of a column in different banks
+  __shared__ float s_o[NW][16][kPad];
+  __shared__ float2 s_ml[NW][MT * 16];
+  __shared__ u32x4 s_q[item_shares_q(D, MT) ? MT * (D / 32) * 64 : 1];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = uniform(tid >> 6);
+  const int items = p.bs * p.num_kv_heads;
+  const int chunk = blockIdx.x / items;
+  const int item = blockIdx.x - chunk * items;
+  const int r = item / p.num_kv_heads;
+  const int total_q = uniform(q_indptr[p.bs]);
+  Item it;
+  it.r = r;
+  it.g = item - r * p.num_kv_heads;
+  it.L = clamp_len(p, seq_lens, r);
+  const int C = chunk_tokens(p, seq_lens, lane);
+  const bool whole = it.L <= C;
+  if (chunk > 0 && (int64_t)chunk * C >= it.L) return;   // no such chunk
+  it.n = spans_of<NB>(it.L);
+  it.arriving = FUSE && is_arriving(p, stage_table, r);
+  q_rows(q_indptr, r, total_q, p.max_q, it.qo, it.nq);
+  it.rows = p.group * it.nq;
+  it.win = it.L - it.nq;
+  // the chunk's spans, shared by the waves
+  const int js = whole ? 0 : chunk * (C / (NB * kBlock));
+  const int ns = whole ? it.n : min(it.n - js, C / (NB * kBlock));
+  it.j0 = js + ns * wave / NW;
+  it.j1 = js + ns * (wave + 1) / NW;
+  if (total_q <= 0) {
+    // no query rows: an arriving request's tiles still move to the worker pool
+    if (it.arriving)
+      for (int j = it.j0; j < it.j1; ++j) {
+        const SpanRef<NB> s = make_ref<NB, true>(
+            p, it, j, load_ids<NB, true>(p, block_table, stage_table, it, j));
+        KOps<D, NB> k;
+        VOps<D, NB> v;
+        load_k<D, NB>(k, s, lane);
+        load_v<D, NB>(v, s, lane);
+        store_k<D, NB>(k, p, s, lane);
+        store_v<D, NB>(v, p, s, lane);
+      }
+    return;
+  }
+  Acc<D, MT> a;
+  init_acc<D, MT>(a, p, it, lane);
+  if (FUSE && it.arriving)
+    item_spans<D, MT, FUSE>(p, block_table, stage_table, it, total_q, a, s_q, wave, lane);
+  else
+    item_spans<D, MT, false>(p, block_table, stage_table, it, total_q, a, s_q, wave, lane);
+  // each row's maximum and sum over the waves, then each wave's share of it
+  const int64_t prow = ((int64_t)item * p.split + chunk) * (MT * 16);
+  const int grp = lane >> 4, row = lane & 15;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    a.l[mt] = wave_sum_groups(a.l[mt]);
+    if (grp == 0) s_ml[wave][mt * 16 + row] = make_float2(a.m[mt], a.l[mt]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    float mx = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) mx = fmaxf(mx, s_ml[w][mt * 16 + row].x);
+    const float msub = mx == -INFINITY ? 0.f : mx;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float2 ml = s_ml[w][mt * 16 + row];
+      sum += __builtin_amdgcn_exp2f(ml.x - msub) * ml.y;
+    }
+    const float f = sum > 0.f ? __builtin_amdgcn_exp2f(a.m[mt] - msub) / sum : 0.f;
+    if (!whole && tid < 16) p.part_ml[prow + mt * 16 + row] = make_float2(mx, sum);
+    if (mt > 0) __syncthreads();   // the previous tile's sums have been read
+#pragma unroll
+    for (int dt = 0; dt < D / 16; ++dt)
+      *(f32x4*)&s_o[wave][row][dt * 16 + grp * 4] = a.o[mt][dt] * f;
+    __syncthreads();
+    const int orow = tid / (D / 8), c = tid % (D / 8);
+    const int m = mt * 16 + orow;
+    if (orow < 16 && m < it.rows) {
+      f32x4 lo = f32x4{0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        lo += *(const f32x4*)&s_o[w][orow][c * 8];
+        hi += *(const f32x4*)&s_o[w][orow][c * 8 + 4];
+      }
+      const bf16x2 b0 = {(__bf16)lo[0], (__bf16)lo[1]}, b1 = {(__bf16)lo[2], (__bf16)lo[3]};
+      const bf16x2 b2 = {(__bf16)hi[0], (__bf16)hi[1]}, b3 = {(__bf16)hi[2], (__bf16)hi[3]};
+      const int j = m / p.group, h = it.g * p.group + m % p.group;
+      uint16_t* dst = whole ? p.out + ((int64_t)(it.qo + j) * p.num_q_heads + h) * D
+                            : p.part_o + (prow + m) * D;
+      *(u32x4*)(dst + c * 8) =
+          u32x4{__builtin_bit_cast(uint32_t, b0), __builtin_bit_cast(uint32_t, b1),
+                __builtin_bit_cast(uint32_t, b2), __builtin_bit_cast(uint32_t, b3)};
+    }
+  }
+}
+
 // One wave's running merge of partial rows: a lane holds 8 columns of one row.
 struct MergeAcc {
   float m, l;
@@ -1188,73 +1423,95 @@ __device__ inline void merge_into(MergeAcc& a, float m, float l, float scale,
 
 constexpr int kMergeMaxSplit = 16;   // waves that share the parts of one row group
 
-// Merge the partials of every item that a range boundary cut, in range order
-// (deterministic, no atomics).  A wave owns a group of 64 / (D / 8) rows, a
-// lane 8 columns of a row (one 16-byte load per part).
+// Merge the partials of every cut item, in order (deterministic, no atomics).
+// A wave owns a group of 64 / (D / 8) rows, a lane 8 columns of a row (one
+// 16-byte load per part).
 //
-// BY_ITEM: one workgroup per (item, row group); its waves take the item's
-// parts in turn and their merges meet in LDS.  Used where the items are so
-// few that each is cut into several parts: an item's parts are then read in
-// parallel and its row groups go to different CUs.  Otherwise one workgroup
-// per range (of each segment), a wave per row group: it finishes the item the
-// range cuts at its end, if that item began in the range, from the range's
-// record.  Latency is the bound of both: the launch, one round of loads that
-// says which item it is, one that brings the parts.  Against one workgroup
-// per range that walked an item's parts two at a time: a single request of
-// 32001 tokens (8 items of about 100 parts) 53.1 -> 8.1 us, 24 requests of
-// 1000-4000 tokens (32/8 heads) 11.2 -> 6.0 us, the fused pass of 32 requests
-// 12.5 -> 6.2 us; by range, the fused verify_8b pass 11.8 -> 9.3 us and the
-// 512-request decode 6.7 -> 4.7 us.
-template <int D, int MT, bool BY_ITEM>
+// kByChunk (after item_attention_kernel) and kByItem: one workgroup per (item,
+// row group); its waves take the item's parts in turn and their merges meet in
+// LDS, so an item's parts are read in parallel and its row groups go to
+// different CUs.  kByRange: one workgroup per range (of each segment), a wave
+// per row group: it finishes the item the range cuts at its end, if that item
+// began in the range, from the range's record.  Latency is the bound of all:
+// the launch, one round of loads that says which item it is, one that brings
+// the parts.  Against one workgroup per range that walked an item's parts two
+// at a time: the fused pass of 32 requests (1024-4096 tokens) 12.5 -> 6.2 us
+// by item, the fused verify_8b pass 11.8 -> 9.3 us and the 512-request decode
+// 6.7 -> 4.7 us by range.
+enum MergeMode { kByChunk, kByItem, kByRange };
+
+template <int D, int MT, int MODE>
 __global__ __launch_bounds__(1024) void combine_kernel(Params p) {
+  constexpr bool ITEM = MODE != kByRange;
   constexpr int kLanes = D / 8;            // lanes per row
   constexpr int kRows = 64 / kLanes;       // rows per wave
   const int lane = threadIdx.x & 63;
   const int wave = uniform(threadIdx.x >> 6);
   const int waves = blockDim.x >> 6;
   const int hkv = p.num_kv_heads;
-  // all independent loads: the row count, the batch's spans, the item
   const int total_q = p.q_indptr[p.bs];
-  const uint4 head = *(const uint4*)p.head;
-  int64_t base, ra;
-  int n, g, qo, nq;
-  bool seg_b;
-  if constexpr (BY_ITEM) {
+  int g, qo, nq;
+  int64_t ra, rb;          // the item's first and last part
+  int64_t slot0 = 0;       // ITEM: the item's first slot
+  int64_t qoff = 0;        // ranges before the segment's
+  bool sparse = false;     // a part's range may hold no span
+  int64_t T = 1, W = 1;
+  int w_odd = p.w_odd;
+  if constexpr (ITEM) {
     const int r = blockIdx.x / hkv;
     g = blockIdx.x - r * hkv;
-    const uint2 rq = p.req[r];
-    n = (int)rq.y;
     q_rows(p.q_indptr, r, total_q, p.max_q, qo, nq);
-    base = (int64_t)hkv * rq.x + (int64_t)g * n;
-    seg_b = rq.x >= head.x;
-  } else {
-    seg_b = blockIdx.x >= p.merge_waves;
-    ra = seg_b ? blockIdx.x - p.merge_waves : blockIdx.x;
-    const CutRec rec = p.cut_rec[ra + (seg_b ? p.num_waves : 0)];
-    // no wave took this range (its record is stale), or it leaves nothing
-    if (ra >= head.z || rec.n < 0) return;
-    n = rec.n;
-    g = rec.g;
-    qo = rec.qo;
-    nq = min(rec.nq, max(0, total_q - qo));
-    base = rec.base;
+    if constexpr (MODE == kByChunk) {
+      const int C = chunk_tokens(p, p.seq_lens, lane);
+      const int L = clamp_len(p, p.seq_lens, r);
+      ra = 0;
+      rb = (L + (int64_t)C - 1) / C - 1;
+      slot0 = (int64_t)blockIdx.x * p.split;
+    }
   }
-  if (total_q <= 0 || nq <= 0) return;   // (the main kernel attended nothing and wrote nothing)
-  const int64_t T = (int64_t)hkv * (seg_b ? head.y : head.x), W = head.z;
-  const int64_t qoff = seg_b ? p.num_waves : 0;
-  const Ranges R(T, W, p.w_even, seg_b ? p.w_odd_b : p.w_odd);
-  if (seg_b) base -= (int64_t)hkv * head.x;
-  if constexpr (BY_ITEM) ra = R.of(base);
-  const int64_t rb = R.of(base + n - 1);
-  if (rb <= ra) return;                  // one range holds the whole item
+  if constexpr (MODE != kByChunk) {
+    if (total_q <= 0) return;    // (the main kernel attended nothing and wrote no record)
+    const uint4 head = *(const uint4*)p.head;
+    W = head.z;
+    bool seg_b;
+    int64_t base;
+    int n;
+    if constexpr (MODE == kByItem) {
+      const uint2 rq = p.req[blockIdx.x / hkv];
+      n = (int)rq.y;
+      base = (int64_t)hkv * rq.x + (int64_t)g * n;
+      seg_b = rq.x >= head.x;
+    } else {
+      seg_b = blockIdx.x >= p.merge_waves;
+      ra = seg_b ? blockIdx.x - p.merge_waves : blockIdx.x;
+      const CutRec rec = p.cut_rec[ra + (seg_b ? p.num_waves : 0)];
+      // no wave took this range (its record is stale), or it leaves nothing
+      if (ra >= W || rec.n < 0) return;
+      n = rec.n;
+      g = rec.g;
+      qo = rec.qo;
+      nq = min(rec.nq, max(0, total_q - qo));
+      base = rec.base;
+    }
+    T = (int64_t)hkv * (seg_b ? head.y : head.x);
+    if (seg_b) {
+      base -= (int64_t)hkv * head.x;
+      qoff = p.num_waves;
+      w_odd = p.w_odd_b;
+    }
+    const Ranges R(T, W, p.w_even, w_odd);
+    if constexpr (MODE == kByItem) ra = R.of(base);
+    rb = R.of(base + n - 1);
+    // ranges without a span exist only where spans are as few as waves
+    sparse = T < 2 * W;
+  }
+  if (total_q <= 0 || nq <= 0 || rb <= ra) return;   // nothing attended, or one part holds it all
   const int rows = p.group * nq;
-  const int m0 = (BY_ITEM ? (int)blockIdx.y : wave) * kRows;
-  if (m0 >= rows) return;                // (uniform over the workgroup when BY_ITEM)
-  const int split = BY_ITEM ? waves : 1, s0 = BY_ITEM ? wave : 0;
+  const int m0 = (ITEM ? (int)blockIdx.y : wave) * kRows;
+  if (m0 >= rows) return;                // (uniform over the workgroup when ITEM)
+  const int split = ITEM ? waves : 1, s0 = ITEM ? wave : 0;
   const int m = m0 + lane / kLanes, c = lane % kLanes;
   const int mld = min(m, rows - 1);      // loads clamped into the item's rows
-  // ranges without a span exist only where spans are as few as waves
-  const bool sparse = T < 2 * W;
   MergeAcc acc;
   merge_init(acc);
   constexpr int kAhead = 4;              // parts loaded before the first is merged
@@ -1264,14 +1521,19 @@ __global__ __launch_bounds__(1024) void combine_kernel(Params p) {
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       const int64_t q = min(rb, q0 + (int64_t)u * split);
-      const int64_t row = (2 * (qoff + q) + (q > ra ? 0 : 1)) * (MT * 16) + mld;
+      const int64_t slot = MODE == kByChunk ? slot0 + q : 2 * (qoff + q) + (q > ra ? 0 : 1);
+      const int64_t row = slot * (MT * 16) + mld;
       ml[u] = p.part_ml[row];
       w[u] = *(const u32x4*)(p.part_o + row * D + c * 8);
     }
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       const int64_t q = q0 + (int64_t)u * split;
-      if (q > rb || (sparse && R.begin(q) >= R.end(q))) continue;
+      if (q > rb) continue;
+      if (MODE != kByChunk && sparse) {
+        const Ranges R(T, W, p.w_even, w_odd);
+        if (R.begin(q) >= R.end(q)) continue;
+      }
       // bf16 to fp32 by placing each half in the high bits (exact)
       float o[8];
 #pragma unroll
@@ -1282,7 +1544,7 @@ __global__ __launch_bounds__(1024) void combine_kernel(Params p) {
       merge_into(acc, ml[u].x, ml[u].y, ml[u].y, o);   // the part's rows are O / sum
     }
   }
-  if constexpr (BY_ITEM) {
+  if constexpr (ITEM) {
     // the waves' merges meet in LDS, in wave order
     extern __shared__ float s_part[];      // [waves][10][64]
     float* mine = s_part + wave * 640 + lane;
@@ -1340,7 +1602,7 @@ struct Plan {
   int mt;            // 16-row tiles
   int num_waves;     // W: resident waves of the launch
   size_t lds_bytes;  // dynamic LDS of the span prefix and work order
-  size_t prefix_bytes, part_o_bytes, part_ml_bytes, cut_rec_bytes, ws_bytes;
+  size_t head_bytes, part_o_bytes, part_ml_bytes, cut_rec_bytes, ws_bytes;
 };
 
 // Launch facts of one kernel instantiation on one device, queried once per
@@ -1441,36 +1703,53 @@ bool make_plan(int bs, int hq, int hkv, int d, int max_q, int max_seq_len, bool 
   pl->num_waves = resident_waves(d, pl->mt, fuse, (pl->lds_bytes + 15) / 16 * 16);
   // a head and a tail slot per range, W ranges in each of the two segments
   const size_t slots = 4 * (size_t)pl->num_waves * pl->mt * 16;
-  pl->prefix_bytes = (16 + (size_t)bs * sizeof(uint2) + 255) / 256 * 256;
+  pl->head_bytes = (16 + (size_t)bs * sizeof(uint2) + 255) / 256 * 256;
   pl->part_o_bytes = slots * d * sizeof(uint16_t);
   pl->part_ml_bytes = slots * sizeof(float2);
   pl->cut_rec_bytes = 2 * (size_t)pl->num_waves * sizeof(CutRec);
-  pl->ws_bytes = pl->prefix_bytes + pl->part_o_bytes + pl->part_ml_bytes + pl->cut_rec_bytes;
+  pl->ws_bytes = pl->head_bytes + pl->part_o_bytes + pl->part_ml_bytes + pl->cut_rec_bytes;
   return true;
+}
+
+// Row groups (of the merge's waves) of the largest item.
+template <int D>
+int row_groups(const Params& p) {
+  return (p.group * p.max_q + 64 / (D / 8) - 1) / (64 / (D / 8));
+}
+
+// The merge by item, with about one wave for every two of an item's parts.
+template <int D, int MT, int MODE>
+void launch_merge(const Params& p, uint32_t items, int parts, hipStream_t stream) {
+  int split = 1;
+  while (split < kMergeMaxSplit && 2 * split < parts) split *= 2;
+  hipLaunchKernelGGL((combine_kernel<D, MT, MODE>), dim3(items, row_groups<D>(p)),
+                     dim3(64 * split), (size_t)split * 640 * sizeof(float), stream, p);
 }
 
 template <int D, int MT, bool FUSE>
 void launch(const Params& p, int bs, size_t lds_bytes, hipStream_t stream) {
+  const uint32_t items = (uint32_t)bs * p.num_kv_heads;
+  if (p.split > 0) {
+    hipLaunchKernelGGL((item_attention_kernel<D, MT, FUSE>), dim3(items * p.split),
+                       dim3(kItemWaves * 64), 0, stream, p, p.block_table, p.stage_table,
+                       p.seq_lens, p.q_indptr);
+    if (p.split == 1) return;
+    launch_merge<D, MT, kByChunk>(p, items, p.split, stream);
+    return;
+  }
   hipLaunchKernelGGL((verify_attention_kernel<D, MT, FUSE>), dim3(p.num_waves / 4), dim3(256),
                      lds_bytes, stream, p, p.block_table, p.stage_table, p.seq_lens,
                      p.q_indptr);
-  // the merge: by item where the ranges are at least twice the items (every
-  // item is cut, so every workgroup has work: 24 requests x 8 KV heads 6.0 us
-  // by item, 7.3 us by range; 32 requests fused 6.2 against 8.4 us), with about one wave for every two parts of an
-  // item; by range otherwise (most items of a large batch are whole: 2048
-  // workgroups by range, not 4096 by item and row group)
+  // by item where the ranges are at least twice the items (every item is cut,
+  // so every workgroup has work: 24 requests x 8 KV heads 6.0 us by item, 7.3
+  // by range; 32 requests fused 6.2 against 8.4 us); by range otherwise (most
+  // items of a large batch are whole)
   const int64_t ranges = (int64_t)(FUSE ? 2 : 1) * p.merge_waves;
-  const int64_t items = (int64_t)bs * p.num_kv_heads;
-  const int groups = (p.group * p.max_q + 64 / (D / 8) - 1) / (64 / (D / 8));
-  if (2 * items <= ranges) {
-    int split = 1;
-    while (split < kMergeMaxSplit && 4 * items * split <= ranges) split *= 2;
-    hipLaunchKernelGGL((combine_kernel<D, MT, true>), dim3((uint32_t)items, groups),
-                       dim3(64 * split), (size_t)split * 640 * sizeof(float), stream, p);
-  } else {
-    hipLaunchKernelGGL((combine_kernel<D, MT, false>), dim3((uint32_t)ranges), dim3(64 * groups),
-                       0, stream, p);
-  }
+  if (2 * (int64_t)items <= ranges)
+    launch_merge<D, MT, kByItem>(p, items, (int)(ranges / items), stream);
+  else
+    hipLaunchKernelGGL((combine_kernel<D, MT, kByRange>), dim3((uint32_t)ranges),
+                       dim3(64 * row_groups<D>(p)), 0, stream, p);
 }
 
 template <int D, bool FUSE>
@@ -1481,6 +1760,48 @@ void launch_d(const Params& p, int mt, int bs, size_t lds_bytes, hipStream_t str
     case 3: launch<D, 3, FUSE>(p, bs, lds_bytes, stream); break;
     default: launch<D, 4, FUSE>(p, bs, lds_bytes, stream); break;
   }
+}
+
+// How a batch runs: the most chunks the item kernel cuts an item into (1: none
+// is cut), or 0 for the wave-split kernel.  items = requests x KV heads, b =
+// K/V bytes of the longest context the call can hold per item, two_waves:
+// the tile keeps two waves per SIMD, slots: partial slots of the workspace.
+//
+// The item kernel has no prologue over the batch, no merge launch when nothing
+// is cut, and the hardware hands its workgroups to free CUs; but an item's
+// time is bound by one CU (about 49 bytes per ns), and the
+// fused pass loses the order that keeps the writes together.  Lines measured
+// on MI355X (us, wave-split kernel -> item kernel; 32/8 heads, D 128, K = 4
+// unless said; items x longest context, lengths uniform from a quarter of it):
+//   whole items, read only: 192 x 1024 33 -> 18, 256 x 2048 43 -> 35, 256 x
+//     4096 62 -> 59 (384 x 4096 89 -> 94, 512 x 4096 118 -> 120), 512 x 2048
+//     67 -> 61 (1024 x 2048, 16/8 heads, K = 0: 107 -> 109), 1024 x 1024
+//     70 -> 62, 4096 x 512 (16/8, K = 0) 118 -> 108;
+//   cut items, read only: 8 x 32001 39 -> 31, 8 x 4096 21 -> 14, 64 x 4096
+//     32 -> 27, 128 x 4096 45 -> 41, 64 x 16000 even (128 x 16000 124 -> 133);
+//   whole items, fused, 30 % arriving: 32 x 256 30 -> 9, 256 x 1024 49 -> 31,
+//     256 x 2048 61 -> 51 (512 x 2048 98 -> 102), 512 x 1024 66 -> 56 (2048 x
+//     1024 179 -> 186), 2048 x 512 108 -> 97;
+//   cut items, fused: 32 x 1024 35 -> 13, 32 x 4096 37 -> 20, 64 x 4096
+//     44 -> 33, 128 x 4096 60 -> 57 (128 x 16000 180 -> 214);
+//   64 rows at head_dim 128 (one wave per SIMD): 512 x 1024 57 -> 52 (2048 x
+//     1024 173 -> 179, 64 x 4096 41 -> 56).
+int item_split(int64_t items, int64_t b, bool two_waves, bool fuse, int cus, int64_t slots) {
+  constexpr int64_t KB = 1024, MB = 1024 * KB;
+  const int64_t total = items * b;
+  const int few = two_waves ? cus / 2 : cus / 16;   // so few items leave CUs idle: cut them
+  if (items <= few && b > (fuse && two_waves ? 256 : 512) * KB) {
+    const bool cut = !two_waves ? total <= 64 * MB
+                     : fuse     ? b <= 2 * MB || total <= 150 * MB
+                                : total <= 400 * MB;
+    if (!cut) return 0;
+    // twice the workgroups aimed at: the longest context may take two shares
+    return (int)std::max<int64_t>(1, std::min(slots / items, (4 * cus + items - 1) / items));
+  }
+  if (!two_waves) return b <= 512 * KB && items <= 2 * cus;
+  if (fuse)
+    return b <= 256 * KB || (b <= 512 * KB && items <= 2 * cus) || (b <= MB && items <= cus);
+  return b <= 512 * KB || (b <= MB && items <= 2 * cus) || (b <= 2 * MB && items <= cus);
 }
 
 // Shared by both entry points: validation, workspace carving, launch.
@@ -1553,9 +1874,9 @@ nsd_status run(const char* fn, bool fuse, const void* q, const void* k_cache,
   char* ws = (char*)workspace;
   p.head = (uint32_t*)ws;
   p.req = (uint2*)(ws + 16);
-  p.part_o = (uint16_t*)(ws + pl.prefix_bytes);
-  p.part_ml = (float2*)(ws + pl.prefix_bytes + pl.part_o_bytes);
-  p.cut_rec = (CutRec*)(ws + pl.prefix_bytes + pl.part_o_bytes + pl.part_ml_bytes);
+  p.part_o = (uint16_t*)(ws + pl.head_bytes);
+  p.part_ml = (float2*)(ws + pl.head_bytes + pl.part_o_bytes);
+  p.cut_rec = (CutRec*)(ws + pl.head_bytes + pl.part_o_bytes + pl.part_ml_bytes);
   p.num_blocks = (int32_t)num_blocks;
   p.stage_blocks = fuse ? (int32_t)stage_blocks : 0;
   p.bs = bs;
@@ -1580,6 +1901,11 @@ nsd_status run(const char* fn, bool fuse, const void* q, const void* k_cache,
   p.w_odd = 94;
   p.w_odd_b = 91;
   p.scale_log2 = scale * 1.4426950408889634f;
+  p.split_groups = 2 * ki.cus;
+  p.split = g_waves_override.load(std::memory_order_relaxed) > 0
+                ? 0
+                : item_split((int64_t)bs * num_kv_heads, most * head_dim * 4, head_dim * pl.mt <= 384,
+                             fuse, ki.cus, 4 * (int64_t)pl.num_waves);
   p.out_off = (int32_t)pre_bytes;
   p.out_cap = (int32_t)per_wave;
   const size_t lds_bytes = pre_bytes + 4 * per_wave;
