@@ -2,11 +2,15 @@
 
 Thin argument marshalling over the C ABI declared in ``include/nebulasd.h``:
 torch tensors are checked (dtype, device, contiguity, shapes) and passed as
-raw device pointers together with torch's current HIP stream.  Every step of
-the round runs in the library's HIP kernels; there is no fallback, and a
-missing library raises at the first call.
+raw device pointers together with torch's current HIP stream.  The calls of a
+round go through the native marshalling module (``csrc/torch_binding.cpp``);
+arguments it does not take (a failed check, unusual argument types) come back
+to the Python code below, which makes the same call through ctypes or names
+the fault.  Every step of the round runs in the library's HIP kernels; there
+is no fallback, and a missing library raises at the first call.
 """
 import ctypes
+import importlib.util
 import math
 import os
 
@@ -76,6 +80,36 @@ def lib():
             f.restype, f.argtypes = res, args
         _lib = l
     return _lib
+
+
+BINDING_PATH = os.path.join(HERE, "_nsd_torch.so")
+# the library's entry points the marshalling module calls, in its order
+_BOUND = ("nsd_kv_gather", "nsd_verify_attention", "nsd_gather_verify_attention",
+          "nsd_verify_attention_workspace_size", "nsd_spec_accept",
+          "nsd_spec_accept_workspace_size", "nsd_sample", "nsd_kv_append", "nsd_commit_lengths")
+_native_module = None
+
+
+def _native():
+    """The marshalling module, bound to the loaded library."""
+    global _native_module
+    if _native_module is None:
+        l = lib()
+        if not os.path.exists(BINDING_PATH):
+            raise RuntimeError(f"{BINDING_PATH} is not built: run `python -c \"import "
+                               f"__graft_entry__ as g; g.build()\"` at the repository root")
+        spec = importlib.util.spec_from_file_location("_nsd_torch", BINDING_PATH)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        m.bind(tuple(ctypes.cast(getattr(l, f), ctypes.c_void_p).value for f in _BOUND))
+        _native_module = m
+    return _native_module
+
+
+def _raised(r):
+    """A native call's library error, (entry point, status), raised."""
+    if r.__class__ is tuple:
+        _check(*r)
 
 
 def _check(fn, status):
@@ -172,6 +206,11 @@ def kv_gather(src_k, src_v, dst_k, dst_v, src_ids, dst_ids, layer0=0, n_layers=N
     Planes: K [layers][blocks][Hkv][D/8][16][8], V [layers][blocks][Hkv][D][16] bf16
     (a 5-d tensor is taken as a single layer).  src_ids/dst_ids: int32 [n_pairs].
     """
+    r = (_native_module or _native()).kv_gather(src_k, src_v, dst_k, dst_v, src_ids, dst_ids,
+                                                layer0, n_layers)
+    if r is not None:
+        _raised(r)
+        return dst_k, dst_v
     planes = [src_k, src_v, dst_k, dst_v]
     if src_k.dim() == 5:
         planes = [t.unsqueeze(0) for t in planes]
@@ -226,6 +265,12 @@ def verify_attention(q, k_cache, v_cache, block_table, seq_lens, q_indptr, max_q
     block_table int32 [bs][max_blocks]; seq_lens int32 [bs]; q_indptr int32 [bs+1].
     max_q_per_seq / max_seq_len are host-side bounds of n_q and L_r.
     """
+    r = (_native_module or _native()).verify_attention(
+        q, k_cache, v_cache, block_table, seq_lens, q_indptr, max_q_per_seq, max_seq_len, scale,
+        out, workspace)
+    if r is not None:
+        _raised(r)
+        return r
     _dev(q, torch.bfloat16, "q")
     _dev(k_cache, torch.bfloat16, "k_cache")
     _dev(v_cache, torch.bfloat16, "v_cache")
@@ -264,6 +309,12 @@ def gather_verify_attention(q, k_cache, v_cache, k_stage, v_stage, block_table, 
     staging planes and leave them in k_cache/v_cache at block_table[r][b];
     returns out [total_q][Hq][D] bf16.
     """
+    r = (_native_module or _native()).gather_verify_attention(
+        q, k_cache, v_cache, k_stage, v_stage, block_table, stage_table, seq_lens, q_indptr,
+        max_q_per_seq, max_seq_len, scale, out, workspace)
+    if r is not None:
+        _raised(r)
+        return r
     for t, n in ((q, "q"), (k_cache, "k_cache"), (v_cache, "v_cache"), (k_stage, "k_stage"),
                  (v_stage, "v_stage")):
         _dev(t, torch.bfloat16, n)
@@ -320,6 +371,12 @@ def spec_accept(p_target, q_draft, draft_tokens, uniforms, q_indptr, max_k, acce
 
     workspace: a GPU tensor of at least accept_workspace_size(bs, vocab) bytes
     (allocated per call when None)."""
+    r = (_native_module or _native()).spec_accept(p_target, q_draft, draft_tokens, uniforms,
+                                                  q_indptr, max_k, accepted_len, out_tokens,
+                                                  workspace)
+    if r is not None:
+        _raised(r)
+        return r[0], r[1]
     _dev(p_target, torch.float32, "p_target")
     _dev(uniforms, torch.float32, "uniforms")
     _dev(q_indptr, torch.int32, "q_indptr")
@@ -383,6 +440,10 @@ def sample(probs, uniforms, out=None, workspace=None):
     possibly strided (e.g. ``draft_tokens.view(bs, K)[:, i]``); workspace: at
     least accept_workspace_size(n, V) bytes (allocated per call when None).
     Returns out."""
+    r = (_native_module or _native()).sample(probs, uniforms, out, workspace)
+    if r is not None:
+        _raised(r)
+        return r
     if probs.dtype != torch.float32 or not probs.is_cuda or probs.dim() != 2:
         raise TypeError("probs must be a 2-d fp32 GPU tensor")
     n, vocab = probs.shape
@@ -439,6 +500,10 @@ def copy_plan(src, dst, copies, chunk_bytes=DEFAULT_CHUNK, stream=None, window_b
 
 def kv_append(k_pool, v_pool, k_new, v_new, block_table, seq_lens, q_indptr):
     """Write the window rows k_new/v_new [total_q][Hkv][D] into their paged slots (one layer)."""
+    r = (_native_module or _native()).kv_append(k_pool, v_pool, k_new, v_new, block_table,
+                                                seq_lens, q_indptr)
+    if r is not None:
+        return _raised(r)
     for t, n in ((k_pool, "k_pool"), (v_pool, "v_pool"), (k_new, "k_new"), (v_new, "v_new")):
         _dev(t, torch.bfloat16, n)
     for t, n in ((block_table, "block_table"), (seq_lens, "seq_lens"), (q_indptr, "q_indptr")):
@@ -459,6 +524,10 @@ def kv_append(k_pool, v_pool, k_new, v_new, block_table, seq_lens, q_indptr):
 
 def commit_lengths(seq_lens, q_indptr, accepted_len, out=None):
     """Committed lengths seq_lens - K + accepted_len (int32 [bs])."""
+    r = (_native_module or _native()).commit_lengths(seq_lens, q_indptr, accepted_len, out)
+    if r is not None:
+        _raised(r)
+        return r
     for t, n in ((seq_lens, "seq_lens"), (q_indptr, "q_indptr"), (accepted_len, "accepted_len")):
         _dev(t, torch.int32, n)
     bs = seq_lens.numel()

@@ -1,7 +1,10 @@
-"""Build libnebulasd.so for gfx950 with hipcc (in-tree, no JIT cache)."""
+"""Build libnebulasd.so for gfx950 with hipcc, and the torch marshalling module
+(in-tree, no JIT cache)."""
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -14,6 +17,9 @@ SOURCES = ["status.cpp", "kv_gather.hip", "verify_attention.hip", "spec_accept.h
 # bandwidth probes for the measurement of practical ceilings: a library of their own
 PROBE_SOURCES = ["hbm_probe.hip"]
 PROBE_LIB_PATH = os.path.join(HERE, "libnsd_probe.so")
+# the torch marshalling module (host code)
+BINDING_SOURCE = "torch_binding.cpp"
+BINDING_PATH = os.path.join(HERE, "_nsd_torch.so")
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CFLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
@@ -40,13 +46,33 @@ def _link(objs, path):
     os.replace(tmp, path)
 
 
+def _build_binding():
+    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+    tmp = BINDING_PATH + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-I{os.path.join(ROOT, 'include')}",
+           "-isystem", os.path.join(torch_dir, "include"),
+           "-isystem", os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
+           f"-I{sysconfig.get_paths()['include']}", os.path.join(CSRC, BINDING_SOURCE),
+           "-o", tmp, f"-L{os.path.join(torch_dir, 'lib')}", "-ltorch_python", "-ltorch",
+           "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"compiling {BINDING_SOURCE} failed:\n{r.stderr}")
+    os.replace(tmp, BINDING_PATH)
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source and link the shared libraries (the round's library
-    and the bandwidth probes); returns the round library's path."""
+    """Compile every source and link the shared libraries (the round's library,
+    the bandwidth probes and the torch marshalling module); returns the round
+    library's path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = SOURCES + PROBE_SOURCES
     with ThreadPoolExecutor(max_workers=min(4, len(srcs))) as ex:
+        binding = ex.submit(_build_binding)
         objs = dict(zip(srcs, ex.map(_compile, srcs)))
+        binding.result()
     _link([objs[s] for s in SOURCES], LIB_PATH)
     _link([objs[s] for s in PROBE_SOURCES], PROBE_LIB_PATH)
     if verbose:

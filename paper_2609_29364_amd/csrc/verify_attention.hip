@@ -810,11 +810,12 @@ struct Ranges {
 // spread over every resident wave cuts each item into one-span parts whose
 // merge costs more than the streaming (a one-request round ran in 65 us on
 // 1024 waves and 29 us on 64); too few waves leave HBM idle.  Measured on
-// MI355X: the separate attention (four-block spans) is best at about one
-// wave per 20 blocks; the fused pass at B / (15 + B / 1000) waves (about 15
-// blocks per wave at 1k blocks, 30 at 10-20k, 80 at 60k), and with every
-// resident wave once that passes 7/8 of them.  Every kernel derives the
-// same count from the segments' spans.
+// MI355X with the merge by item: the separate attention is best at about one
+// wave per 8 blocks (8 x 4096 tokens, 32/8 heads, 26.0 us at one per 20, 21.7
+// at one per 8), the fused pass at B / (6 + B / 1000) waves (4 requests of
+// 4000-16000 tokens 74 us at B / (15 + B / 1000), 58 so; 8 requests 106 and
+// 97), and with every resident wave once that passes 7/8 of them.  Every
+// kernel derives the same count from the segments' spans.
 constexpr int kMinWaves = 64;
 constexpr int kMinCopyWaves = 64;   // surplus waves that take over the fused pass's pool writes
 
@@ -826,7 +827,7 @@ __device__ inline int64_t segment_blocks(int64_t ta, int64_t tb) {
 // Non-decreasing in B (the host bounds the count by the longest context).
 template <bool FUSE>
 __host__ __device__ inline int64_t waves_for(int64_t B, int64_t W) {
-  int64_t want = FUSE ? B * 1000 / (15000 + B) : (B + 7) / 8;
+  int64_t want = FUSE ? B * 1000 / (6000 + B) : (B + 7) / 8;
   if (FUSE && 8 * want > 7 * W) want = W;
   want = (want + 3) / 4 * 4;
   if (want < kMinWaves) want = kMinWaves;

@@ -10,13 +10,13 @@ the pool).
 The draft stage that precedes it (Eq. 1) is composed the same way: K steps of
 append, single-query attention and sampling."""
 from . import (kv_gather, verify_attention, gather_verify_attention, spec_accept, kv_append,
-               commit_lengths, sample, accept_workspace_size)
+               commit_lengths, sample, accept_workspace_size, _native, _raised)
 
-# Batches below this many requests prepare with the separate gather even when a
-# stage table is given: there the fused pass is bound by each wave's chain of
-# span steps and measured slower than gather + attention (verify_8b-shaped
-# requests: 4 requests 68 against 50 us, 8 requests 78 against 54 us; from
-# about 16 requests on the fused pass is as fast or faster).
+# Batches below this many requests that also append window rows prepare with the
+# separate gather even when a stage table is given: the rows then go to the pool
+# alone, one append per layer, and the staging bank stays as it was.  (Without
+# window rows the fused pass is the faster one at every size: 4 requests of
+# 1024-4096 tokens 19.6 us against 18.3 for the attention alone.)
 FUSED_MIN_BATCH = 16
 
 
@@ -41,22 +41,33 @@ def verify_round(k_pool, v_pool, k_stage, v_stage, src_ids, dst_ids, q, block_ta
     written there; ``accept_workspace`` is spec_accept's workspace.
 
     ``prepare``: "auto" lets a batch of fewer than FUSED_MIN_BATCH requests
-    given both a stage table and the (src_ids, dst_ids) pairs take the
-    separate gather (the caller states the two describe the same preparation,
-    with ids in range), the faster path for such batches; "fused" keeps the
+    given window rows and both a stage table and the (src_ids, dst_ids) pairs
+    take the separate gather (the caller states the two describe the same
+    preparation, with ids in range); "fused" keeps the
     fused pass whenever a stage table is given; "gather" always gathers first.
     """
     if prepare not in ("auto", "fused", "gather"):
         raise ValueError(f"prepare must be 'auto', 'fused' or 'gather', not {prepare!r}")
     if stage_table is not None and src_ids is not None and (
-            prepare == "gather" or (prepare == "auto" and seq_lens.numel() < FUSED_MIN_BATCH)):
+            prepare == "gather" or (prepare == "auto" and window_kv is not None and
+                                    seq_lens.numel() < FUSED_MIN_BATCH)):
         stage_table = None
-    if stage_table is None:
-        kv_gather(k_stage, v_stage, k_pool, v_pool, src_ids, dst_ids)
-    elif window_kv is not None:
+    if stage_table is not None and window_kv is not None:
         # fused preparation: an arriving request's blocks are still in the staging
         # bank, so its window rows go there and the pass moves whole blocks to the pool
-        pool_table, stage_rows = append_tables or fused_tables(block_table, stage_table)
+        append_tables = append_tables or fused_tables(block_table, stage_table)
+        pool_table, stage_rows = append_tables
+    if out is not None and workspace is not None:
+        # the same calls, submitted natively
+        r = _native().verify_round(
+            k_pool, v_pool, k_stage, v_stage, src_ids, dst_ids, q, block_table, seq_lens,
+            q_indptr, max_q_per_seq, max_seq_len, accept, out, workspace, scale, stage_table,
+            window_kv, committed, append_tables, accept_workspace)
+        if r is not None:
+            _raised(r)
+            return (out, *r) if accept is not None else (out, None, None)
+    if stage_table is None:
+        kv_gather(k_stage, v_stage, k_pool, v_pool, src_ids, dst_ids)
     outs = []
     for layer in range(k_pool.shape[0]):
         o = None if out is None else out[layer]
@@ -134,7 +145,16 @@ def draft_stage(k_pool, v_pool, q, k_new, v_new, probs, uniforms, block_table, l
         if src_ids is not None and src_ids.numel():
             kv_gather(k_stage, v_stage, k_pool, v_pool, src_ids, dst_ids)
     else:
-        pool_table, stage_rows = append_tables or fused_tables(block_table, stage_table)
+        append_tables = append_tables or fused_tables(block_table, stage_table)
+        pool_table, stage_rows = append_tables
+    if workspace is not None:
+        # the same calls, submitted natively
+        r = _native().draft_stage(k_pool, v_pool, q, k_new, v_new, probs, uniforms, block_table,
+                                  lens, q_indptr, max_seq_len, k_stage, v_stage, stage_table,
+                                  tokens, out, workspace, scale, append_tables, sample_workspace)
+        if r is not None:
+            _raised(r)
+            return out, tokens
     for i in range(n_steps):
         if stage_table is not None and i == 0:
             kv_append(k_pool, v_pool, k_new[i], v_new[i], pool_table, lens[i], q_indptr)
