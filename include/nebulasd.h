@@ -338,6 +338,27 @@ nsd_status nsd_kv_append(void* k_pool, void* v_pool, int64_t num_blocks, const v
                          void* stream);
 
 /*
+ * nsd_kv_append of n_layers layers in one launch (one per 32 layers), into two
+ * banks: layer l's rows k_new[l] / v_new[l] (host arrays of n_layers device
+ * pointers) go to planes stacked over layers, k_pool / v_pool
+ * [n_layers][num_blocks][...] through block_table, and k_stage / v_stage
+ * [n_layers][stage_num_blocks][...] through stage_rows (the fused
+ * preparation's staging bank; an entry out of range, such as -1, is skipped in
+ * either).  stage_rows == NULL or stage_num_blocks == 0: no second bank.
+ * Everything else as in nsd_kv_append.
+ *
+ * Passage: Section 3, as nsd_kv_append.
+ */
+nsd_status nsd_kv_append_layers(void* k_pool, void* v_pool, int64_t num_blocks,
+                                const int32_t* block_table, void* k_stage, void* v_stage,
+                                int64_t stage_num_blocks, const int32_t* stage_rows,
+                                int32_t n_layers, const void* const* k_new,
+                                const void* const* v_new, int32_t max_blocks_per_seq,
+                                const int32_t* seq_lens, const int32_t* q_indptr, int32_t bs,
+                                int32_t total_q, int32_t num_kv_heads, int32_t block_size,
+                                int32_t head_dim, void* stream);
+
+/*
  * Commit accepted lengths: new_lens[r] = seq_lens[r] - K_r + n_r, with
  * K_r = q_indptr[r+1] - q_indptr[r] - 1 and n_r = accepted_len[r] clamped to
  * [0, K_r].  The request keeps its anchor and its accepted proposals; the
@@ -414,6 +435,19 @@ nsd_status nsd_spec_accept(const float* p_target, const float* q_draft,
                            size_t workspace_bytes, void* stream);
 
 /*
+ * nsd_spec_accept and nsd_commit_lengths in one call: new_lens[r] is the length
+ * request r commits (seq_lens, new_lens as there; new_lens may alias seq_lens).
+ *
+ * Passage: Sections 1 and 3, as nsd_commit_lengths.
+ */
+nsd_status nsd_spec_accept_commit(const float* p_target, const float* q_draft,
+                                  const int32_t* draft_tokens, const float* uniforms,
+                                  const int32_t* q_indptr, int32_t bs, int32_t vocab,
+                                  int32_t max_k, int32_t* accepted_len, int32_t* out_tokens,
+                                  const int32_t* seq_lens, int32_t* new_lens, void* workspace,
+                                  size_t workspace_bytes, void* stream);
+
+/*
  * nsd_spec_accept without a workspace argument, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation).  Same arguments, semantics and results
@@ -458,6 +492,20 @@ nsd_status nsd_spec_accept_static(const float* p_target, const float* q_draft,
 nsd_status nsd_sample(const float* probs, int64_t row_stride, const float* uniforms,
                       int32_t n_rows, int32_t vocab, int32_t* out_tokens, int32_t out_stride,
                       void* workspace, size_t workspace_bytes, void* stream);
+
+/*
+ * nsd_sample of `steps` consecutive rows for each of n requests: request b's
+ * step i reads probs[b * row_stride + i * vocab ...] with uniforms[i * n + b]
+ * and writes out_tokens[b * out_stride + i] (row_stride >= steps * vocab,
+ * out_stride >= steps).  workspace: nsd_spec_accept_workspace_size(n * steps,
+ * vocab) bytes; everything else as in nsd_sample.
+ *
+ * Passage: Eq. 1, as nsd_sample.
+ */
+nsd_status nsd_sample_steps(const float* probs, int64_t row_stride, const float* uniforms,
+                            int32_t n, int32_t steps, int32_t vocab, int32_t* out_tokens,
+                            int32_t out_stride, void* workspace, size_t workspace_bytes,
+                            void* stream);
 
 /*
  * Host validation of a round's metadata: host copies of the arrays the

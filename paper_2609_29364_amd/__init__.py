@@ -57,6 +57,11 @@ _SIGS = {
     "nsd_kv_append": (_I32, [_P, _P, _I64, _P, _P, _P, _I32, _P, _P, _I32, _I32, _I32, _I32, _I32,
                              _P]),
     "nsd_commit_lengths": (_I32, [_P, _P, _P, _P, _I32, _P]),
+    "nsd_kv_append_layers": (_I32, [_P, _P, _I64, _P, _P, _P, _I64, _P, _I32, _P, _P, _I32, _P,
+                                    _P, _I32, _I32, _I32, _I32, _I32, _P]),
+    "nsd_spec_accept_commit": (_I32, [_P, _P, _P, _P, _P, _I32, _I32, _I32, _P, _P, _P, _P, _P,
+                                      _SZ, _P]),
+    "nsd_sample_steps": (_I32, [_P, _I64, _P, _I32, _I32, _I32, _P, _I32, _P, _SZ, _P]),
     "nsd_host_alias": (_I32, [_P, ctypes.POINTER(ctypes.c_void_p)]),
     "nsd_spec_accept_static": (_I32, [_P, _P, _P, _P, _P, _I32, _I32, _I32, _P, _P, _P]),
     "nsd_spec_accept_static_max_bytes": (_SZ, []),
@@ -86,7 +91,8 @@ BINDING_PATH = os.path.join(HERE, "_nsd_torch.so")
 # the library's entry points the marshalling module calls, in its order
 _BOUND = ("nsd_kv_gather", "nsd_verify_attention", "nsd_gather_verify_attention",
           "nsd_verify_attention_workspace_size", "nsd_spec_accept",
-          "nsd_spec_accept_workspace_size", "nsd_sample", "nsd_kv_append", "nsd_commit_lengths")
+          "nsd_spec_accept_workspace_size", "nsd_sample", "nsd_kv_append", "nsd_commit_lengths",
+          "nsd_kv_append_layers", "nsd_spec_accept_commit", "nsd_sample_steps")
 _native_module = None
 
 

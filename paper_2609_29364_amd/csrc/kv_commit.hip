@@ -8,99 +8,145 @@
 // its n_r accepted proposals: L'_r = L_r - K_r + n_r (the resampled or bonus
 // token is the next round's anchor).
 //
-// kv_append: one workgroup per (KV head, request).  Memory writes whole
+// kv_append: one workgroup per (KV head, request, layer).  Memory writes whole
 // 32-byte sectors cheaply and partial ones with a read-modify-write in the
 // memory system, which also delays the kernels that follow (a decode
 // attention launched right after an append made of 2-byte element stores
 // ran 6 % slower).  So the kernel writes whole sectors only: for every block
-// the window touches, thread d rewrites dimension d's 16-slot V row (32
-// bytes) and thread (run c, slot pair) the two 16-byte K runs of a slot
-// pair, taking the window's slots from the new rows and every other slot
-// from the sector's current contents.  Only this workgroup writes the
+// the window touches, thread d < head_dim rewrites dimension d's 16-slot V row
+// (32 bytes) and thread head_dim + (run c, slot pair) the two 16-byte K runs
+// of a slot pair, taking the window's slots from the new rows and every other
+// slot from the sector's current contents.  Only this workgroup writes the
 // (block, KV head) tile, so the merge needs no ordering.  Volume: the
 // sectors the window touches, read and written (about 4.5 KiB each way per
 // (request, KV head) for a one-token window at head_dim 128, 13 MB each way
 // for a verify_8b layer's five-token windows).
+//
+// Latency bounds it (offsets, block id, sector, store, once per block), so a
+// round appends all its layers, into the pool and the staging bank, in one
+// launch, the new rows are loaded while the ids arrive, unconditionally, and K
+// and V go to different threads.  Four layers of 32 requests (five-token windows,
+// 10 of them staged): eight launches of 6.4 to 6.9 us -> one of 9.3 us; one
+// layer of 64 requests (one token) into pool and staging bank 2 x 4.7 -> 5.2 us.
 #include "nsd_internal.h"
+
+#include <type_traits>
 
 namespace {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-// 32 bytes as 16 bf16 (two 16-byte accesses)
-struct Sector {
-  uint16_t e[16];
+constexpr int kAppendLayers = 32;   // layers of one launch (their rows are kernel arguments)
+
+// The paged planes a window goes to, stacked over layers, and the block table
+// that says where (a negative id: not here).
+struct Bank {
+  uint16_t* k;
+  uint16_t* v;
+  const int32_t* table;
+  int64_t num_blocks;   // 0: no such bank
 };
 
-__device__ inline Sector load_sector(const uint16_t* p) {
-  Sector s;
-  const u32x4 a = ((const u32x4*)p)[0], b = ((const u32x4*)p)[1];
-  __builtin_memcpy(&s.e[0], &a, 16);
-  __builtin_memcpy(&s.e[8], &b, 16);
-  return s;
-}
+// LAYERS and BANKS: the most a launch takes (one layer into one bank is the
+// draft step's call).
+template <int LAYERS, int BANKS>
+struct AppendArgs {
+  Bank bank[BANKS];
+  const uint16_t* k_new[LAYERS];
+  const uint16_t* v_new[LAYERS];
+  int32_t max_blocks_per_seq, num_kv_heads, head_dim, total_q;
+  int32_t aligned;              // every k_new is 16-byte aligned
+};
 
-__device__ inline void store_sector(uint16_t* p, const Sector& s) {
-  u32x4 a, b;
-  __builtin_memcpy(&a, &s.e[0], 16);
-  __builtin_memcpy(&b, &s.e[8], 16);
-  ((u32x4*)p)[0] = a;
-  ((u32x4*)p)[1] = b;
-}
-
-__global__ __launch_bounds__(128) void kv_append_kernel(
-    uint16_t* __restrict__ k_pool, uint16_t* __restrict__ v_pool,
-    const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new,
-    const int32_t* __restrict__ block_table, const int32_t* __restrict__ seq_lens,
-    const int32_t* __restrict__ q_indptr, int64_t num_blocks, int32_t max_blocks_per_seq,
-    int32_t num_kv_heads, int32_t head_dim, int32_t total_q) {
+template <int LAYERS, int BANKS>
+__global__ __launch_bounds__(256) void kv_append_kernel(
+    AppendArgs<LAYERS, BANKS> A, const int32_t* __restrict__ table0, const int32_t* __restrict__ table1,
+    const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ q_indptr) {
   const int g = blockIdx.x;
   const int r = blockIdx.y;
+  const int layer = LAYERS == 1 ? 0 : blockIdx.z;
   const int tid = threadIdx.x;
+  const int d = A.head_dim, hkv = A.num_kv_heads;
   const int a = q_indptr[r];
   const int nq = q_indptr[r + 1] - a;
   const int L = seq_lens[r];
   if (nq <= 0) return;
   // window positions inside [0, 16 * max_blocks_per_seq)
   const int64_t t0 = max((int64_t)L - nq, (int64_t)0);
-  const int64_t t1 = min((int64_t)L - 1, (int64_t)max_blocks_per_seq * 16 - 1);
-  const int runs = head_dim / 8;
+  const int64_t t1 = min((int64_t)L - 1, (int64_t)A.max_blocks_per_seq * 16 - 1);
+  const int64_t row_len = (int64_t)hkv * d;
+  const uint16_t* kn = A.k_new[layer] + (int64_t)g * d;
+  const uint16_t* vn = A.v_new[layer] + (int64_t)g * d;
   for (int64_t blk = t0 / 16; blk <= t1 / 16 && t0 <= t1; ++blk) {
-    const int32_t id = block_table[(int64_t)r * max_blocks_per_seq + blk];
-    if (id < 0 || id >= num_blocks) continue;   // an invalid id is not written
-    const int s_lo = (int)(max(t0, blk * 16) - blk * 16);
-    const int s_hi = (int)(min(t1, blk * 16 + 15) - blk * 16);
-    const int64_t tile = ((int64_t)id * num_kv_heads + g) * head_dim * 16;
-    // the window row of slot s (a row outside [0, total_q) leaves the slot)
-    auto row_of = [&](int s) -> int64_t {
-      const int64_t row = (int64_t)a + (blk * 16 + s) - ((int64_t)L - nq);
-      return row >= 0 && row < total_q ? row : -1;
-    };
-    if (tid < head_dim) {
-      uint16_t* vp = v_pool + tile + (int64_t)tid * 16;
-      Sector row = load_sector(vp);
+    const int64_t entry = (int64_t)r * A.max_blocks_per_seq + blk;
+    const int32_t id[2] = {table0[entry], BANKS == 2 ? table1[entry] : -1};
+    // the window's slots of the block; slot s takes row first + s (a row
+    // outside [0, total_q) leaves its slot)
+    const int64_t first = (int64_t)a + blk * 16 - ((int64_t)L - nq);
+    const int s_lo = (int)max(max(t0 - blk * 16, (int64_t)0), min((int64_t)16, -first));
+    const int s_hi = (int)min(min(t1 - blk * 16, (int64_t)15),
+                              max((int64_t)-1, (int64_t)A.total_q - 1 - first));
+    if (s_lo > s_hi) continue;
+    // this thread's 32-byte sector: the new elements w at the bits m
+    uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0}, m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    int64_t off;
+    const bool is_v = tid < d;
+    if (is_v) {
+      off = (int64_t)tid * 16;
+      for (int s0 = s_lo; s0 <= s_hi; s0 += 4) {
+        uint32_t x[4];
 #pragma unroll
-      for (int s = 0; s < 16; ++s) {   // fixed indices keep the sector in registers
-        const int64_t q = s >= s_lo && s <= s_hi ? row_of(s) : -1;
-        if (q >= 0) row.e[s] = v_new[(q * num_kv_heads + g) * head_dim + tid];
+        for (int u = 0; u < 4; ++u) x[u] = vn[(first + min(s0 + u, s_hi)) * row_len + tid];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int s = s0 + u;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {   // fixed indices keep the sector in registers
+            const bool here = s <= s_hi && i == s / 2;
+            const uint32_t bits = here ? 0xffffu << (s % 2 * 16) : 0u;
+            m[i] |= bits;
+            w[i] |= (x[u] * 0x10001u) & bits;
+          }
+        }
       }
-      store_sector(vp, row);
-    }
-    const int p_lo = s_lo / 2, np = s_hi / 2 - p_lo + 1;
-    if (tid < runs * np) {
-      const int c = tid % runs, pr = p_lo + tid / runs;
-      uint16_t* kp = k_pool + tile + (int64_t)(c * 16 + 2 * pr) * 8;
-      Sector run2 = load_sector(kp);
+    } else {
+      const int runs = d / 8;
+      const int c = (tid - d) % runs, pr = s_lo / 2 + (tid - d) / runs;
+      if (pr > s_hi / 2) continue;
+      off = (int64_t)(c * 16 + 2 * pr) * 8;
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int s = 2 * pr + u;
-        const int64_t q = s >= s_lo && s <= s_hi ? row_of(s) : -1;
-        if (q < 0) continue;
-        const uint16_t* src = k_new + (q * num_kv_heads + g) * head_dim + c * 8;
+        const uint32_t bits = s >= s_lo && s <= s_hi ? 0xffffffffu : 0u;
+        const uint16_t* src = kn + (first + min(max(s, s_lo), s_hi)) * row_len + c * 8;
+        u32x4 x;
+        if (A.aligned) {
+          x = *(const u32x4*)src;
+        } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) run2.e[u * 8 + e] = src[e];
+          for (int e = 0; e < 4; ++e) x[e] = src[2 * e] | (uint32_t)src[2 * e + 1] << 16;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          w[u * 4 + e] = x[e] & bits;
+          m[u * 4 + e] = bits;
+        }
       }
-      store_sector(kp, run2);
+    }
+#pragma unroll
+    for (int b = 0; b < BANKS; ++b) {
+      const Bank& to = A.bank[b];
+      if (id[b] < 0 || id[b] >= to.num_blocks) continue;   // an invalid id is not written
+      const int64_t tile = (((int64_t)layer * to.num_blocks + id[b]) * hkv + g) * d * 16;
+      u32x4* p = (u32x4*)((is_v ? to.v : to.k) + tile + off);
+      u32x4 lo = p[0], hi = p[1];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        lo[e] = (lo[e] & ~m[e]) | w[e];
+        hi[e] = (hi[e] & ~m[4 + e]) | w[4 + e];
+      }
+      p[0] = lo;
+      p[1] = hi;
     }
   }
 }
@@ -118,32 +164,89 @@ __global__ __launch_bounds__(256) void commit_kernel(const int32_t* __restrict__
 
 }  // namespace
 
+static nsd_status append_layers(const char* fn, const Bank* banks, int32_t n_layers,
+                                const void* const* k_new, const void* const* v_new,
+                                int32_t max_blocks_per_seq, const int32_t* seq_lens,
+                                const int32_t* q_indptr, int32_t bs, int32_t total_q,
+                                int32_t num_kv_heads, int32_t block_size, int32_t head_dim,
+                                void* stream) {
+  using namespace nsd;
+  const bool second = banks[1].table && banks[1].num_blocks > 0;
+  if (block_size != NSD_BLOCK_SIZE)
+    return fail(NSD_ERR_UNSUPPORTED, "%s: block_size must be 16 (got %d)", fn, block_size);
+  if (head_dim != 64 && head_dim != 128)
+    return fail(NSD_ERR_UNSUPPORTED, "%s: head_dim must be 64 or 128 (got %d)", fn, head_dim);
+  if (bs < 0 || total_q < 0 || num_kv_heads < 1 || num_kv_heads > 65535 || bs > 65535 ||
+      max_blocks_per_seq < 1 || banks[0].num_blocks < 0 || banks[1].num_blocks < 0 || n_layers < 0)
+    return fail(NSD_ERR_SHAPE, "%s: bad sizes", fn);
+  if (bs == 0 || total_q == 0 || n_layers == 0) return NSD_OK;
+  if (!banks[0].k || !banks[0].v || !k_new || !v_new || !banks[0].table || !seq_lens ||
+      !q_indptr || (second && (!banks[1].k || !banks[1].v)))
+    return fail(NSD_ERR_NULL, "%s: NULL pointer argument", fn);
+  for (int l = 0; l < n_layers; ++l)
+    if (!k_new[l] || !v_new[l]) return fail(NSD_ERR_NULL, "%s: NULL pointer argument", fn);
+  if (((uintptr_t)banks[0].k | (uintptr_t)banks[0].v) % 16)
+    return fail(NSD_ERR_SHAPE, "%s: k_pool and v_pool must be 16-byte aligned", fn);
+  if (second && ((uintptr_t)banks[1].k | (uintptr_t)banks[1].v) % 16)
+    return fail(NSD_ERR_SHAPE, "%s: k_stage and v_stage must be 16-byte aligned", fn);
+  clear_stale_error();
+  for (int l0 = 0; l0 < n_layers; l0 += kAppendLayers) {
+    const int n = n_layers - l0 < kAppendLayers ? n_layers - l0 : kAppendLayers;
+    auto go = [&](auto layers, auto bank_count) {
+      constexpr int kLayers = decltype(layers)::value, kBanks = decltype(bank_count)::value;
+      AppendArgs<kLayers, kBanks> A;
+      for (int b = 0; b < kBanks; ++b) {
+        A.bank[b] = b == 0 || second ? banks[b] : Bank{nullptr, nullptr, nullptr, 0};
+        const int64_t before = l0 * A.bank[b].num_blocks * num_kv_heads * head_dim * 16;
+        A.bank[b].k += before;
+        A.bank[b].v += before;
+      }
+      A.aligned = 1;
+      for (int l = 0; l < kLayers; ++l) {
+        A.k_new[l] = l < n ? (const uint16_t*)k_new[l0 + l] : nullptr;
+        A.v_new[l] = l < n ? (const uint16_t*)v_new[l0 + l] : nullptr;
+        if ((uintptr_t)A.k_new[l] % 16) A.aligned = 0;
+      }
+      A.max_blocks_per_seq = max_blocks_per_seq;
+      A.num_kv_heads = num_kv_heads;
+      A.head_dim = head_dim;
+      A.total_q = total_q;
+      hipLaunchKernelGGL((kv_append_kernel<kLayers, kBanks>), dim3(num_kv_heads, bs, n),
+                         dim3(2 * head_dim), 0, (hipStream_t)stream, A, banks[0].table,
+                         second ? banks[1].table : banks[0].table, seq_lens, q_indptr);
+    };
+    if (n_layers == 1 && !second)
+      go(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
+    else
+      go(std::integral_constant<int, kAppendLayers>{}, std::integral_constant<int, 2>{});
+  }
+  return check_launch(fn);
+}
+
 extern "C" nsd_status nsd_kv_append(void* k_pool, void* v_pool, int64_t num_blocks,
                                     const void* k_new, const void* v_new,
                                     const int32_t* block_table, int32_t max_blocks_per_seq,
                                     const int32_t* seq_lens, const int32_t* q_indptr,
                                     int32_t bs, int32_t total_q, int32_t num_kv_heads,
                                     int32_t block_size, int32_t head_dim, void* stream) {
-  using namespace nsd;
-  const char* fn = "kv_append";
-  if (block_size != NSD_BLOCK_SIZE)
-    return fail(NSD_ERR_UNSUPPORTED, "%s: block_size must be 16 (got %d)", fn, block_size);
-  if (head_dim != 64 && head_dim != 128)
-    return fail(NSD_ERR_UNSUPPORTED, "%s: head_dim must be 64 or 128 (got %d)", fn, head_dim);
-  if (bs < 0 || total_q < 0 || num_kv_heads < 1 || num_kv_heads > 65535 || bs > 65535 ||
-      max_blocks_per_seq < 1 || num_blocks < 0)
-    return fail(NSD_ERR_SHAPE, "%s: bad sizes", fn);
-  if (bs == 0 || total_q == 0) return NSD_OK;
-  if (!k_pool || !v_pool || !k_new || !v_new || !block_table || !seq_lens || !q_indptr)
-    return fail(NSD_ERR_NULL, "%s: NULL pointer argument", fn);
-  if (((uintptr_t)k_pool | (uintptr_t)v_pool) % 16)
-    return fail(NSD_ERR_SHAPE, "%s: k_pool and v_pool must be 16-byte aligned", fn);
-  clear_stale_error();
-  hipLaunchKernelGGL(kv_append_kernel, dim3(num_kv_heads, bs), dim3(128), 0, (hipStream_t)stream,
-                     (uint16_t*)k_pool, (uint16_t*)v_pool, (const uint16_t*)k_new,
-                     (const uint16_t*)v_new, block_table, seq_lens, q_indptr, num_blocks,
-                     max_blocks_per_seq, num_kv_heads, head_dim, total_q);
-  return check_launch(fn);
+  const Bank banks[2] = {{(uint16_t*)k_pool, (uint16_t*)v_pool, block_table, num_blocks},
+                         {nullptr, nullptr, nullptr, 0}};
+  return append_layers("kv_append", banks, 1, &k_new, &v_new, max_blocks_per_seq, seq_lens,
+                       q_indptr, bs, total_q, num_kv_heads, block_size, head_dim, stream);
+}
+
+extern "C" nsd_status nsd_kv_append_layers(
+    void* k_pool, void* v_pool, int64_t num_blocks, const int32_t* block_table, void* k_stage,
+    void* v_stage, int64_t stage_num_blocks, const int32_t* stage_rows, int32_t n_layers,
+    const void* const* k_new, const void* const* v_new, int32_t max_blocks_per_seq,
+    const int32_t* seq_lens, const int32_t* q_indptr, int32_t bs, int32_t total_q,
+    int32_t num_kv_heads, int32_t block_size, int32_t head_dim, void* stream) {
+  const Bank banks[2] = {
+      {(uint16_t*)k_pool, (uint16_t*)v_pool, block_table, num_blocks},
+      {(uint16_t*)k_stage, (uint16_t*)v_stage, stage_rows, stage_rows ? stage_num_blocks : 0}};
+  return append_layers("kv_append_layers", banks, n_layers, k_new, v_new, max_blocks_per_seq,
+                       seq_lens, q_indptr, bs, total_q, num_kv_heads, block_size, head_dim,
+                       stream);
 }
 
 extern "C" nsd_status nsd_commit_lengths(const int32_t* seq_lens, const int32_t* q_indptr,

@@ -59,8 +59,11 @@ struct Args {
   const int32_t* q_indptr;     // [rows + 1] (not SAMPLE)
   int32_t rows;                // requests (not SAMPLE) or sample rows
   int32_t vocab, max_k, nchunk;
-  int64_t row_stride;          // SAMPLE: elements between rows
-  int32_t out_stride;          // SAMPLE: entries between output tokens
+  int64_t row_stride;          // SAMPLE: elements between requests' rows
+  int32_t out_stride;          // SAMPLE: entries between requests' output tokens
+  int32_t steps;               // SAMPLE: rows of a request (row r: request r / steps)
+  const int32_t* seq_lens;     // [rows], with committed
+  int32_t* committed;          // [rows] committed lengths, or NULL
   double* ws_sum;              // [rows][nchunk]
   int32_t* ws_n;               // [rows]
   int32_t* accepted_len;
@@ -144,12 +147,17 @@ __device__ inline bool request_rows(const Args& A, int r, int& a, int& k) {
 // Request r's first row a and clamped proposal count k; wave 0 evaluates the
 // acceptance tests and leaves the first rejection n in *s_n.  Returns false
 // when the request has no row (nothing to test or draw).
+// Sample row r's uniform: [steps][requests].
+__device__ inline int sample_uniform(const Args& A, int r) {
+  return r % A.steps * (A.rows / A.steps) + r / A.steps;
+}
+
 template <bool SAMPLE>
 __device__ inline bool acceptance(const Args& A, int r, int lane, int wave, int& a, int& k,
                                   int* s_n, int& x_lane) {
   x_lane = -1;
   if (SAMPLE) {
-    a = r;
+    a = sample_uniform(A, r);
     k = 0;
     return true;
   }
@@ -175,7 +183,16 @@ __device__ inline bool acceptance(const Args& A, int r, int lane, int wave, int&
 
 template <bool SAMPLE>
 __device__ inline const float* row_p(const Args& A, int r, int a, int n) {
-  return SAMPLE ? A.p + (int64_t)r * A.row_stride : A.p + (int64_t)(a + n) * A.vocab;
+  return SAMPLE ? A.p + (int64_t)(r / A.steps) * A.row_stride + (int64_t)(r % A.steps) * A.vocab
+                : A.p + (int64_t)(a + n) * A.vocab;
+}
+
+// Request r's accepted length, and (nsd_commit_lengths) the length it commits.
+__device__ inline void write_length(const Args& A, int r, int n) {
+  A.accepted_len[r] = n;
+  if (!A.committed) return;
+  const int k = max(0, A.q_indptr[r + 1] - A.q_indptr[r] - 1);
+  A.committed[r] = A.seq_lens[r] - k + min(n, k);
 }
 
 // One iteration's loads: chunks c0 + u * NW (u < kUnroll) of the weight
@@ -411,7 +428,7 @@ __device__ inline void draw_wave(const Args& A, int r, int a, int k, int n, doub
     }
   }
   if (SAMPLE) {
-    if (lane == 0) A.out_tokens[(int64_t)r * A.out_stride] = y;
+    if (lane == 0) A.out_tokens[(int64_t)(r / A.steps) * A.out_stride + r % A.steps] = y;
     return;
   }
   if (lane <= k) {
@@ -420,7 +437,7 @@ __device__ inline void draw_wave(const Args& A, int r, int a, int k, int n, doub
     else if (lane == n) tok = y;
     A.out_tokens[a + lane] = tok;
   }
-  if (lane == 0) A.accepted_len[r] = n;
+  if (lane == 0) write_length(A, r, n);
 }
 
 template <bool SAMPLE>
@@ -429,14 +446,16 @@ __global__ __launch_bounds__(kThreads) void pick_kernel(Args A) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int r = blockIdx.x;
-  int a = r, k = 0, n = 0, x_lane = -1;
+  int a = 0, k = 0, n = 0, x_lane = -1;
   if (!SAMPLE) {
     if (!request_rows(A, r, a, k)) {
-      if (tid == 0) A.accepted_len[r] = 0;
+      if (tid == 0) write_length(A, r, 0);
       return;
     }
     n = min(max(A.ws_n[r], 0), k);
     if (tid < k) x_lane = A.x[a - r + tid];
+  } else {
+    a = sample_uniform(A, r);
   }
   const float u_draw = A.u[a + k];
   const double* sums = A.ws_sum + (int64_t)r * A.nchunk;
@@ -459,7 +478,7 @@ __global__ __launch_bounds__(kRowThreads) void accept_row_kernel(Args A) {
   const int r = blockIdx.x;
   int a, k, x_lane;
   if (!acceptance<SAMPLE>(A, r, lane, wave, a, k, &s_n, x_lane)) {
-    if (threadIdx.x == 0) A.accepted_len[r] = 0;
+    if (threadIdx.x == 0) write_length(A, r, 0);
     return;
   }
   int n = 0;
@@ -554,8 +573,9 @@ extern "C" size_t nsd_spec_accept_workspace_size(int32_t rows, int32_t vocab) {
 static nsd_status spec_accept_impl(const char* fn, const float* p_target, const float* q_draft,
                             const int32_t* draft_tokens, const float* uniforms,
                             const int32_t* q_indptr, int32_t bs, int32_t vocab, int32_t max_k,
-                            int32_t* accepted_len, int32_t* out_tokens, void* workspace,
-                            size_t workspace_bytes, void* stream) {
+                            int32_t* accepted_len, int32_t* out_tokens, const int32_t* seq_lens,
+                            int32_t* committed, void* workspace, size_t workspace_bytes,
+                            void* stream) {
   using namespace nsd;
   if (bs < 0 || bs > kMaxRows)
     return fail(NSD_ERR_SHAPE, "%s: bs must be in [0, %d]", fn, kMaxRows);
@@ -571,7 +591,7 @@ static nsd_status spec_accept_impl(const char* fn, const float* p_target, const 
   if (((uintptr_t)p_target | (uintptr_t)(max_k > 0 ? q_draft : p_target)) & 15)
     return fail(NSD_ERR_SHAPE, "%s: probability rows must be 16-byte aligned", fn);
   Args A{p_target, q_draft, draft_tokens, uniforms, q_indptr, bs, vocab, max_k, 0,
-         (int64_t)vocab, 1, nullptr, nullptr, accepted_len, out_tokens};
+         (int64_t)vocab, 1, 1, seq_lens, committed, nullptr, nullptr, accepted_len, out_tokens};
   return launch(false, A, bs, workspace, workspace_bytes, stream, fn);
 }
 
@@ -618,8 +638,22 @@ extern "C" nsd_status nsd_spec_accept(const float* p_target, const float* q_draf
                                       int32_t* out_tokens, void* workspace,
                                       size_t workspace_bytes, void* stream) {
   return spec_accept_impl("spec_accept", p_target, q_draft, draft_tokens, uniforms, q_indptr, bs,
-                          vocab, max_k, accepted_len, out_tokens, workspace, workspace_bytes,
-                          stream);
+                          vocab, max_k, accepted_len, out_tokens, nullptr, nullptr, workspace,
+                          workspace_bytes, stream);
+}
+
+extern "C" nsd_status nsd_spec_accept_commit(const float* p_target, const float* q_draft,
+                                             const int32_t* draft_tokens, const float* uniforms,
+                                             const int32_t* q_indptr, int32_t bs, int32_t vocab,
+                                             int32_t max_k, int32_t* accepted_len,
+                                             int32_t* out_tokens, const int32_t* seq_lens,
+                                             int32_t* new_lens, void* workspace,
+                                             size_t workspace_bytes, void* stream) {
+  if (bs > 0 && (!seq_lens || !new_lens))
+    return nsd::fail(NSD_ERR_NULL, "spec_accept_commit: NULL pointer argument");
+  return spec_accept_impl("spec_accept_commit", p_target, q_draft, draft_tokens, uniforms,
+                          q_indptr, bs, vocab, max_k, accepted_len, out_tokens, seq_lens,
+                          new_lens, workspace, workspace_bytes, stream);
 }
 
 extern "C" size_t nsd_spec_accept_static_max_bytes(void) { return kScratchBytes; }
@@ -642,27 +676,44 @@ extern "C" nsd_status nsd_spec_accept_static(const float* p_target, const float*
     if (st != NSD_OK) return st;
   }
   return spec_accept_impl(fn, p_target, q_draft, draft_tokens, uniforms, q_indptr, bs, vocab,
-                          max_k, accepted_len, out_tokens, ws, kScratchBytes, stream);
+                          max_k, accepted_len, out_tokens, nullptr, nullptr, ws, kScratchBytes,
+                          stream);
+}
+
+static nsd_status sample_impl(const char* fn, const float* probs, int64_t row_stride,
+                              const float* uniforms, int32_t n, int32_t steps, int32_t vocab,
+                              int32_t* out_tokens, int32_t out_stride, void* workspace,
+                              size_t workspace_bytes, void* stream) {
+  using namespace nsd;
+  if (n < 0 || steps < 1 || (int64_t)n * steps > kMaxRows)
+    return fail(NSD_ERR_SHAPE, "%s: the rows must be in [0, %d]", fn, kMaxRows);
+  if (vocab < 4 || vocab > kMaxVocab || vocab % 4)
+    return fail(NSD_ERR_UNSUPPORTED, "%s: vocab must be a multiple of 4 in [4, %d] (got %d)", fn,
+                kMaxVocab, vocab);
+  if (row_stride < (int64_t)steps * vocab || row_stride % 4)
+    return fail(NSD_ERR_SHAPE, "%s: row_stride must be a multiple of 4 and hold the row(s) "
+                "(got %lld)", fn, (long long)row_stride);
+  if (out_stride < steps) return fail(NSD_ERR_SHAPE, "%s: out_stride < %d", fn, steps);
+  if (n == 0) return NSD_OK;
+  if (!probs || !uniforms || !out_tokens) return fail(NSD_ERR_NULL, "%s: NULL pointer argument", fn);
+  if ((uintptr_t)probs & 15) return fail(NSD_ERR_SHAPE, "%s: probs must be 16-byte aligned", fn);
+  Args A{probs, nullptr, nullptr, uniforms, nullptr, n * steps, vocab, 0, 0, row_stride,
+         out_stride, steps, nullptr, nullptr, nullptr, nullptr, nullptr, out_tokens};
+  return launch(true, A, n * steps, workspace, workspace_bytes, stream, fn);
 }
 
 extern "C" nsd_status nsd_sample(const float* probs, int64_t row_stride, const float* uniforms,
                                  int32_t n_rows, int32_t vocab, int32_t* out_tokens,
                                  int32_t out_stride, void* workspace, size_t workspace_bytes,
                                  void* stream) {
-  using namespace nsd;
-  if (n_rows < 0 || n_rows > kMaxRows)
-    return fail(NSD_ERR_SHAPE, "sample: n_rows must be in [0, %d]", kMaxRows);
-  if (vocab < 4 || vocab > kMaxVocab || vocab % 4)
-    return fail(NSD_ERR_UNSUPPORTED, "sample: vocab must be a multiple of 4 in [4, %d] (got %d)",
-                kMaxVocab, vocab);
-  if (row_stride < vocab || row_stride % 4)
-    return fail(NSD_ERR_SHAPE, "sample: row_stride must be a multiple of 4 and >= vocab "
-                "(got %lld)", (long long)row_stride);
-  if (out_stride < 1) return fail(NSD_ERR_SHAPE, "sample: out_stride < 1");
-  if (n_rows == 0) return NSD_OK;
-  if (!probs || !uniforms || !out_tokens) return fail(NSD_ERR_NULL, "sample: NULL pointer argument");
-  if ((uintptr_t)probs & 15) return fail(NSD_ERR_SHAPE, "sample: probs must be 16-byte aligned");
-  Args A{probs, nullptr, nullptr, uniforms, nullptr, n_rows, vocab, 0, 0, row_stride,
-         out_stride, nullptr, nullptr, nullptr, out_tokens};
-  return launch(true, A, n_rows, workspace, workspace_bytes, stream, "sample");
+  return sample_impl("sample", probs, row_stride, uniforms, n_rows, 1, vocab, out_tokens,
+                     out_stride, workspace, workspace_bytes, stream);
+}
+
+extern "C" nsd_status nsd_sample_steps(const float* probs, int64_t row_stride,
+                                       const float* uniforms, int32_t n, int32_t steps,
+                                       int32_t vocab, int32_t* out_tokens, int32_t out_stride,
+                                       void* workspace, size_t workspace_bytes, void* stream) {
+  return sample_impl("sample_steps", probs, row_stride, uniforms, n, steps, vocab, out_tokens,
+                     out_stride, workspace, workspace_bytes, stream);
 }

@@ -39,6 +39,9 @@ struct Api {
   decltype(&nsd_sample) sample;
   decltype(&nsd_kv_append) kv_append;
   decltype(&nsd_commit_lengths) commit_lengths;
+  decltype(&nsd_kv_append_layers) kv_append_layers;
+  decltype(&nsd_spec_accept_commit) spec_accept_commit;
+  decltype(&nsd_sample_steps) sample_steps;
 } api;
 
 // Thrown (before anything is enqueued) for arguments the Python path handles.
@@ -195,6 +198,17 @@ void append(const Planes& pool, const char* kn, const char* vn, const int32_t* t
   check("kv_append",
         api.kv_append(pool.k, pool.v, pool.blocks, kn, vn, table, width, lens, b.indptr, b.bs,
                       total_q, b.hkv, NSD_BLOCK_SIZE, b.d, b.stream));
+}
+
+// The window rows of a round's layers, into the pool and (fused preparation) the
+// staging bank.
+void append_layers(const Batch& b, const Planes& pool, const int32_t* pool_table,
+                   const Planes& stage, const int32_t* stage_rows, int32_t layers,
+                   const void* const* kn, const void* const* vn, int32_t total_q) {
+  check("kv_append_layers",
+        api.kv_append_layers(pool.k, pool.v, pool.blocks, pool_table, stage.k, stage.v,
+                             stage.blocks, stage_rows, layers, kn, vn, b.width, b.lens, b.indptr,
+                             b.bs, total_q, b.hkv, NSD_BLOCK_SIZE, b.d, b.stream));
 }
 
 // Runs f without the interpreter lock; library errors become (entry point, status).
@@ -458,11 +472,6 @@ PyObject* py_commit_lengths(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// Window rows of one layer and the tables they are appended through.
-struct Window {
-  const char *k, *v;
-};
-
 // A tuple or list of n items, or NotHere.
 PyObject** items_of(PyObject* o, Py_ssize_t n) {
   if (!PyTuple_CheckExact(o) && !PyList_CheckExact(o)) throw NotHere();
@@ -504,7 +513,7 @@ PyObject* py_verify_round(PyObject*, PyObject* const* a, Py_ssize_t n) {
     } else {
       g = gather_args(ks, vs, k, v, a[4], a[5]);
     }
-    std::vector<Window> window;
+    std::vector<const void*> k_new, v_new;
     const int32_t *pool_table = b.table, *stage_rows = nullptr;
     if (a[17] != Py_None) {
       PyObject** rows = items_of(a[17], -1);
@@ -514,7 +523,8 @@ PyObject* py_verify_round(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const Tensor &kn = bf16(kv[0]), &vn = bf16(kv[1]);
         need(kn.dim() == 3 && kn.size(0) == total && kn.size(1) == b.hkv && kn.size(2) == b.d &&
              vn.sizes() == kn.sizes());
-        window.push_back(Window{(const char*)kn.data_ptr(), (const char*)vn.data_ptr()});
+        k_new.push_back(kn.data_ptr());
+        v_new.push_back(vn.data_ptr());
       }
       if (fused) {
         PyObject** tables = items_of(a[19], 2);
@@ -544,23 +554,24 @@ PyObject* py_verify_round(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return unlocked(
         [&] {
           if (!fused) gather(g, 0, g.layers, b.stream);
+          // every layer's rows are in hand: one launch appends them all
+          if (!k_new.empty())
+            append_layers(b, pool, pool_table, stage, stage_rows, (int32_t)layers, k_new.data(),
+                          v_new.data(), total);
           for (int64_t l = 0; l < layers; ++l) {
             const Planes here = at_layer(pool, l);
-            if (!window.empty()) {
-              append(here, window[l].k, window[l].v, pool_table, b.width, b.lens, b, total);
-              if (fused && stage.blocks > 0)
-                append(at_layer(stage, l), window[l].k, window[l].v, stage_rows, b.width, b.lens,
-                       b, total);
-            }
             if (fused)
               attend_fused(b, qp + l * rows, here, at_layer(stage, l), op + l * rows);
             else
               attend(b, qp + l * rows, here, op + l * rows);
           }
-          if (accepts) accept(s);
           if (committed)
-            check("commit_lengths",
-                  api.commit_lengths(b.lens, b.indptr, s.len, committed, b.bs, b.stream));
+            check("spec_accept_commit",
+                  api.spec_accept_commit(s.p, s.q, s.x, s.u, s.indptr, s.bs, s.vocab, s.max_k,
+                                         s.len, s.tok, b.lens, committed, s.ws, s.ws_bytes,
+                                         s.stream));
+          else if (accepts)
+            accept(s);
         },
         accepts ? wrap2 : yes, s.out);
   });
@@ -625,22 +636,33 @@ PyObject* py_draft_stage(PyObject*, PyObject* const* a, Py_ssize_t n) {
     int32_t* tp = tok.data_ptr<int32_t>();
     const int32_t vocab = small(p.size(2)), ostride = small(std::max<int64_t>(1, p.size(1)));
     const int64_t row = p.size(1) * vocab;
+    // the draws of all steps in one launch, at the end, if a workspace holds
+    // their sums (the attention's is free by then): for 64 requests x 4 steps at
+    // vocab 151936 four launch pairs of 13.3 us -> one launch of 27.1 us
+    const size_t need_ws = api.accept_ws(small(b.bs * steps), vocab);
+    void* all_ws = swn >= need_ws ? (void*)swp : b.ws_bytes >= need_ws ? (void*)b.ws : nullptr;
+    const size_t all_wn = swn >= need_ws ? swn : b.ws_bytes;
+    if ((uintptr_t)all_ws % 8 || b.bs * steps > (1 << 20)) all_ws = nullptr;
     const int64_t qb = (int64_t)b.bs * b.hq * b.d * 2, nb = (int64_t)b.bs * b.hkv * b.d * 2;
     return unlocked(
         [&] {
           for (int64_t i = 0; i < steps; ++i) {
             b.lens = lp + i * b.bs;
             if (fused && i == 0) {
-              append(pool, kp, vp, pool_table, b.width, b.lens, b, b.bs);
-              if (stage.blocks > 0) append(stage, kp, vp, stage_rows, b.width, b.lens, b, b.bs);
+              const void *k0 = kp, *v0 = vp;
+              append_layers(b, pool, pool_table, stage, stage_rows, 1, &k0, &v0, b.bs);
               attend_fused(b, qp, pool, stage, op);
             } else {
               append(pool, kp + i * nb, vp + i * nb, b.table, b.width, b.lens, b, b.bs);
               attend(b, qp + i * qb, pool, op + i * qb);
             }
+            if (all_ws) continue;
             check("sample", api.sample(pp + i * vocab, b.bs > 1 ? row : vocab, up + i * b.bs, b.bs,
                                        vocab, tp + i, ostride, swp, swn, b.stream));
           }
+          if (all_ws && steps > 0)
+            check("sample", api.sample_steps(pp, row, up, b.bs, (int32_t)steps, vocab, tp, ostride,
+                                             all_ws, all_wn, b.stream));
         },
         yes, nullptr);
   });
