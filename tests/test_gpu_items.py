@@ -62,3 +62,33 @@ def test_items(device, case, fused):
         u16(lay.k_stage)[None], u16(lay.v_stage)[None], u16(lay.k_pool)[None],
         u16(lay.v_pool)[None], meta.src_ids, meta.dst_ids)
     assert np.array_equal(u16(kp)[None], ref_k) and np.array_equal(u16(vp)[None], ref_v)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (16, 2, 128), (8, 1, 64), (4, 2, 64)])
+@pytest.mark.parametrize("fused", [False, True])
+def test_row_tiles(device, hq, hkv, d, fused):
+    """Depths of one batch on both sides of every row-tile edge: each item takes the tiles its
+    rows fill, whole and cut."""
+    group = hq // hkv
+    top = min(8, 64 // group - 1)
+    depth = np.array([k for k in range(top + 1) for _ in range(2)])
+    lens = np.where(np.arange(len(depth)) % 2, 40 + 37 * depth, 600 - 31 * depth)
+    lens[-1] = 5000                                  # cut, beside whole ones
+    for keep in (slice(0, -1), slice(None)):
+        n, k = lens[keep], depth[keep]
+        cfg = custom_config(seed=801, bs=len(n), num_q_heads=hq, num_kv_heads=hkv, head_dim=d,
+                            vocab=0, n_arriving=0, pool_blocks=None, staging_order="shuffled")
+        meta = make_meta(cfg, seq_lens=list(n), depth=k,
+                         arriving=(np.arange(len(n)) % 3 != 1) & fused)
+        lay = make_layer(cfg, meta, 0, device)
+        args = (i32(meta.seq_lens, device), i32(meta.q_indptr, device), meta.max_q,
+                meta.max_seq_len)
+        table = i32(meta.block_table, device)
+        if fused:
+            out = nsd.gather_verify_attention(lay.q, lay.k_pool.clone(), lay.v_pool.clone(),
+                                              lay.k_stage, lay.v_stage, table,
+                                              i32(meta.stage_table, device), *args)
+        else:
+            out = nsd.verify_attention(lay.q, lay.k_pool, lay.v_pool, table, *args)
+        torch.cuda.synchronize()
+        check_attention(meta, lay, out, range(len(n)))
