@@ -642,7 +642,10 @@ PyObject* py_draft_stage(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const size_t need_ws = api.accept_ws(small(b.bs * steps), vocab);
     void* all_ws = swn >= need_ws ? (void*)swp : b.ws_bytes >= need_ws ? (void*)b.ws : nullptr;
     const size_t all_wn = swn >= need_ws ? swn : b.ws_bytes;
-    if ((uintptr_t)all_ws % 8 || b.bs * steps > (1 << 20)) all_ws = nullptr;
+    // (a sample workspace that one step's draw refuses is still refused, there)
+    if ((uintptr_t)all_ws % 8 || b.bs * steps > (1 << 20) || (uintptr_t)swp % 8 ||
+        swn < api.accept_ws(b.bs, vocab))
+      all_ws = nullptr;
     const int64_t qb = (int64_t)b.bs * b.hq * b.d * 2, nb = (int64_t)b.bs * b.hkv * b.d * 2;
     return unlocked(
         [&] {

@@ -113,6 +113,30 @@ def test_draft(device, n_arriving):
     both(call, lay.k_pool, lay.v_pool)
 
 
+def test_draft_small_sample_workspace(device):
+    """A sample workspace too small for one step is refused, whatever the others hold; one for
+    a single step is enough."""
+    cfg = custom_config(seed=34, bs=3, num_q_heads=4, num_kv_heads=2, head_dim=64, vocab=0,
+                        n_arriving=0, pool_blocks=None, ctx_lo=20, ctx_hi=300, k_lo=0, k_hi=0)
+    dd = make_draft(cfg, 3, 40000, device)
+    m, lay = dd.meta, dd.layer
+    ws = nsd.new_workspace(nsd.verify_attention_workspace_size(3, 4, 2, 64, 1, m.max_seq_len),
+                           device)
+    need = nsd.accept_workspace_size(3, 40000)
+
+    def call(size):
+        return draft_stage(lay.k_pool, lay.v_pool, dd.q, dd.k_new, dd.v_new, dd.probs,
+                           dd.uniforms, i32(m.block_table, device), dd.lens,
+                           i32(m.q_indptr, device), m.max_seq_len, workspace=ws,
+                           sample_workspace=torch.empty(size, dtype=torch.uint8,
+                                                        device=device))[1]
+
+    with pytest.raises(nsd.NsdError) as e:
+        call(need - 1)
+    assert e.value.status == 4
+    assert torch.equal(call(need), call(4 * need))
+
+
 def test_faults_raise_the_same(device):
     cfg, meta, (k, v, ks, vs, q) = setup(device)
     table, lens, qi = (i32(x, device) for x in (meta.block_table, meta.seq_lens, meta.q_indptr))
