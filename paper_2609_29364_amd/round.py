@@ -1,14 +1,16 @@
 """One verification round composed on one HIP stream (Algorithm 1: Run starts
 once InputReady, KVReady and WorkerReady hold; on one GPU that join is stream
-order): the KV-state preparation of the arriving requests, then per layer the
-append of the window's new K/V rows (when given) and verification attention,
-then spec_accept and the commit of accepted lengths.  The preparation runs
+order): the KV-state preparation of the arriving requests, the append of the
+window's new K/V rows (when given; of all layers in one launch where the
+caller gives the output and the workspace, else layer by layer), verification
+attention per layer, then spec_accept and the commit of accepted lengths.  The preparation runs
 either as its own gather before the layers, or fused into each layer's
 attention pass (the layer's staged tiles are read once, used and written to
 the pool).
 
 The draft stage that precedes it (Eq. 1) is composed the same way: K steps of
-append, single-query attention and sampling."""
+append, single-query attention and sampling (given a workspace, the draws of
+all steps share one launch at the end where a workspace holds their sums)."""
 from . import (kv_gather, verify_attention, gather_verify_attention, spec_accept, kv_append,
                commit_lengths, sample, accept_workspace_size, _native, _raised)
 
