@@ -14,11 +14,14 @@ all steps share one launch at the end where a workspace holds their sums)."""
 from . import (kv_gather, verify_attention, gather_verify_attention, spec_accept, kv_append,
                commit_lengths, sample, accept_workspace_size, _native, _raised)
 
-# Batches below this many requests that also append window rows prepare with the
-# separate gather even when a stage table is given: the rows then go to the pool
-# alone, one append per layer, and the staging bank stays as it was.  (Without
-# window rows the fused pass is the faster one at every size: 4 requests of
-# 1024-4096 tokens 19.6 us against 18.3 for the attention alone.)
+# Batches below this many requests prepare with the separate gather even when a
+# stage table is given: every pair is then moved, blocks past a request's context
+# too, and the staging bank stays as it was.  Which way is faster depends on the
+# contexts (rounds of 4 layers, 32/8 heads, head_dim 128, a third of the requests
+# arriving, gather -> fused, us): 64-512 tokens, 1 request 42 -> 46, 4 45 -> 47, 15
+# 55 -> 56; 1024-4096 tokens, 1 request 72 -> 63, 4 98 -> 99, 8 138 -> 127, 15 247
+# -> 225; with window rows 4 to 8 more each.  A caller whose pairs name no other
+# blocks than the contexts' and whose contexts are long asks for "fused".
 FUSED_MIN_BATCH = 16
 
 
@@ -43,15 +46,16 @@ def verify_round(k_pool, v_pool, k_stage, v_stage, src_ids, dst_ids, q, block_ta
     written there; ``accept_workspace`` is spec_accept's workspace.
 
     ``prepare``: "auto" lets a batch of fewer than FUSED_MIN_BATCH requests
-    given window rows and both a stage table and the (src_ids, dst_ids) pairs
-    take the separate gather (the caller states the two describe the same
-    preparation, with ids in range); "fused" keeps the
+    given both a stage table and the (src_ids, dst_ids) pairs take the separate
+    gather (the caller states the two describe the same preparation, with ids
+    in range; the gather moves every pair, the fused pass the blocks up to each
+    request's context); "fused" keeps the
     fused pass whenever a stage table is given; "gather" always gathers first.
     """
     if prepare not in ("auto", "fused", "gather"):
         raise ValueError(f"prepare must be 'auto', 'fused' or 'gather', not {prepare!r}")
     if stage_table is not None and src_ids is not None and (
-            prepare == "gather" or (prepare == "auto" and window_kv is not None and
+            prepare == "gather" or (prepare == "auto" and
                                     seq_lens.numel() < FUSED_MIN_BATCH)):
         stage_table = None
     if stage_table is not None and window_kv is not None:
