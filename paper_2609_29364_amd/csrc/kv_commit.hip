@@ -13,21 +13,25 @@
 // memory system, which also delays the kernels that follow (a decode
 // attention launched right after an append made of 2-byte element stores
 // ran 6 % slower).  So the kernel writes whole sectors only: for every block
-// the window touches, thread d < head_dim rewrites dimension d's 16-slot V row
-// (32 bytes) and thread head_dim + (run c, slot pair) the two 16-byte K runs
-// of a slot pair, taking the window's slots from the new rows and every other
-// slot from the sector's current contents.  Only this workgroup writes the
+// the window touches, thread t < head_dim rewrites dimension t's 16-slot V row
+// (32 bytes) and, as (run c, slot pair), the two 16-byte K runs of a slot pair
+// that the window touches, taking the window's slots from the new rows and every
+// other slot from the sector's current contents.  Only this workgroup writes the
 // (block, KV head) tile, so the merge needs no ordering.  Volume: the
 // sectors the window touches, read and written (about 4.5 KiB each way per
 // (request, KV head) for a one-token window at head_dim 128, 13 MB each way
 // for a verify_8b layer's five-token windows).
 //
-// Latency bounds it (offsets, block id, sector, store, once per block), so a
-// round appends all its layers, into the pool and the staging bank, in one
-// launch, the new rows are loaded while the ids arrive, unconditionally, and K
-// and V go to different threads.  Four layers of 32 requests (five-token windows,
-// 10 of them staged): eight launches of 6.4 to 6.9 us -> one of 9.3 us; one
-// layer of 64 requests (one token) into pool and staging bank 2 x 4.7 -> 5.2 us.
+// Latency bounds small batches (offsets, block id, sector, store, once per block),
+// so a round appends all its layers, into the pool and the staging bank, in one
+// launch, and the new rows are loaded while the ids arrive.  Large ones are bound
+// by the workgroups in flight, so both planes are one set of head_dim threads: a
+// second set for K left most of its threads idle and a device's worth of wave
+// slots short (8 KV heads, head_dim 128: one-token windows of 512 requests 14.5 us
+// with it, 10.3 without, 256 requests 8.8 and 6.9; five-token windows of 256 12.6
+// and 10.5, of 32 4.4 and 4.5).  Four layers of 32 requests (five-token windows,
+// 10 of them staged): eight launches of 6.4 to 6.9 us -> one of 8.0 us; one layer
+// of 64 requests (one token) into pool and staging bank 2 x 4.7 -> 4.2 us.
 #include "nsd_internal.h"
 
 #include <type_traits>
@@ -58,8 +62,20 @@ struct AppendArgs {
   int32_t aligned;              // every k_new is 16-byte aligned
 };
 
+// Sector p of a plane: the elements at bits m become w.
+__device__ inline void merge_sector(u32x4* p, u32x4 lo, u32x4 hi, const uint32_t (&w)[8],
+                                    const uint32_t (&m)[8]) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    lo[e] = (lo[e] & ~m[e]) | w[e];
+    hi[e] = (hi[e] & ~m[4 + e]) | w[4 + e];
+  }
+  p[0] = lo;
+  p[1] = hi;
+}
+
 template <int LAYERS, int BANKS>
-__global__ __launch_bounds__(256) void kv_append_kernel(
+__global__ __launch_bounds__(128) void kv_append_kernel(
     AppendArgs<LAYERS, BANKS> A, const int32_t* __restrict__ table0, const int32_t* __restrict__ table1,
     const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ q_indptr) {
   const int g = blockIdx.x;
@@ -77,6 +93,7 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
   const int64_t row_len = (int64_t)hkv * d;
   const uint16_t* kn = A.k_new[layer] + (int64_t)g * d;
   const uint16_t* vn = A.v_new[layer] + (int64_t)g * d;
+  const int runs = d / 8, c = tid % runs;
   for (int64_t blk = t0 / 16; blk <= t1 / 16 && t0 <= t1; ++blk) {
     const int64_t entry = (int64_t)r * A.max_blocks_per_seq + blk;
     const int32_t id[2] = {table0[entry], BANKS == 2 ? table1[entry] : -1};
@@ -87,50 +104,51 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
     const int s_hi = (int)min(min(t1 - blk * 16, (int64_t)15),
                               max((int64_t)-1, (int64_t)A.total_q - 1 - first));
     if (s_lo > s_hi) continue;
-    // this thread's 32-byte sector: the new elements w at the bits m
-    uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0}, m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    int64_t off;
-    const bool is_v = tid < d;
-    if (is_v) {
-      off = (int64_t)tid * 16;
-      for (int s0 = s_lo; s0 <= s_hi; s0 += 4) {
-        uint32_t x[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = vn[(first + min(s0 + u, s_hi)) * row_len + tid];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int s = s0 + u;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {   // fixed indices keep the sector in registers
-            const bool here = s <= s_hi && i == s / 2;
-            const uint32_t bits = here ? 0xffffu << (s % 2 * 16) : 0u;
-            m[i] |= bits;
-            w[i] |= (x[u] * 0x10001u) & bits;
-          }
-        }
-      }
-    } else {
-      const int runs = d / 8;
-      const int c = (tid - d) % runs, pr = s_lo / 2 + (tid - d) / runs;
-      if (pr > s_hi / 2) continue;
-      off = (int64_t)(c * 16 + 2 * pr) * 8;
+    // K: the runs of this thread's slot pair, where the window has that many pairs
+    // (a load that the others skip: loaded by all, it cost one-token windows 12 %)
+    const int pr = s_lo / 2 + tid / runs;
+    const bool has_k = pr <= s_hi / 2;
+    u32x4 x[2] = {};
+    if (has_k) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const int s = 2 * pr + u;
-        const uint32_t bits = s >= s_lo && s <= s_hi ? 0xffffffffu : 0u;
-        const uint16_t* src = kn + (first + min(max(s, s_lo), s_hi)) * row_len + c * 8;
-        u32x4 x;
+        const uint16_t* src = kn + (first + min(max(2 * pr + u, s_lo), s_hi)) * row_len + c * 8;
         if (A.aligned) {
-          x = *(const u32x4*)src;
+          x[u] = *(const u32x4*)src;
         } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = src[2 * e] | (uint32_t)src[2 * e + 1] << 16;
+          for (int e = 0; e < 4; ++e) x[u][e] = src[2 * e] | (uint32_t)src[2 * e + 1] << 16;
         }
+      }
+    }
+    // V: dimension tid's slots, w the new elements at the bits m
+    uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0}, m[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          w[u * 4 + e] = x[e] & bits;
-          m[u * 4 + e] = bits;
-        }
+    for (int i = 0; i < 8; ++i)
+      m[i] = (2 * i >= s_lo && 2 * i <= s_hi ? 0xffffu : 0u) |
+             (2 * i + 1 >= s_lo && 2 * i + 1 <= s_hi ? 0xffff0000u : 0u);
+    auto put = [&](int s, uint32_t v) {
+      const uint32_t e = v << (s % 2 * 16);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) w[i] |= i == s / 2 ? e : 0u;   // fixed indices: registers
+    };
+    int s = s_lo;
+    for (; s + 3 <= s_hi; s += 4) {
+      uint32_t v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = vn[(first + s + u) * row_len + tid];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) put(s + u, v[u]);
+    }
+    for (; s <= s_hi; ++s) put(s, vn[(first + s) * row_len + tid]);
+    uint32_t kw[8], km[8];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const uint32_t bits = 2 * pr + u >= s_lo && 2 * pr + u <= s_hi ? 0xffffffffu : 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        kw[u * 4 + e] = x[u][e] & bits;
+        km[u * 4 + e] = bits;
       }
     }
 #pragma unroll
@@ -138,15 +156,16 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
       const Bank& to = A.bank[b];
       if (id[b] < 0 || id[b] >= to.num_blocks) continue;   // an invalid id is not written
       const int64_t tile = (((int64_t)layer * to.num_blocks + id[b]) * hkv + g) * d * 16;
-      u32x4* p = (u32x4*)((is_v ? to.v : to.k) + tile + off);
-      u32x4 lo = p[0], hi = p[1];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        lo[e] = (lo[e] & ~m[e]) | w[e];
-        hi[e] = (hi[e] & ~m[4 + e]) | w[4 + e];
+      u32x4* vp = (u32x4*)(to.v + tile + (int64_t)tid * 16);
+      u32x4* kp = (u32x4*)(to.k + tile + (int64_t)(c * 16 + 2 * pr) * 8);
+      const u32x4 v0 = vp[0], v1 = vp[1];
+      u32x4 k0 = {}, k1 = {};
+      if (has_k) {
+        k0 = kp[0];
+        k1 = kp[1];
       }
-      p[0] = lo;
-      p[1] = hi;
+      merge_sector(vp, v0, v1, w, m);
+      if (has_k) merge_sector(kp, k0, k1, kw, km);
     }
   }
 }
@@ -212,7 +231,7 @@ static nsd_status append_layers(const char* fn, const Bank* banks, int32_t n_lay
       A.head_dim = head_dim;
       A.total_q = total_q;
       hipLaunchKernelGGL((kv_append_kernel<kLayers, kBanks>), dim3(num_kv_heads, bs, n),
-                         dim3(2 * head_dim), 0, (hipStream_t)stream, A, banks[0].table,
+                         dim3(head_dim), 0, (hipStream_t)stream, A, banks[0].table,
                          second ? banks[1].table : banks[0].table, seq_lens, q_indptr);
     };
     if (n_layers == 1 && !second)
