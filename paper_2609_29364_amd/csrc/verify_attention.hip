@@ -57,14 +57,15 @@
 //   partial) go to the wave's LDS buffer, which is written out, in whole
 //   rows, when it is full and when the wave's work ends.  (The fused
 //   variant's own tile stores are the preparation itself and stay in line.)
-// * Short contexts and small batches take another kernel (item_split says
-//   which): a workgroup per (request, KV head), its four waves sharing the
-//   item's spans and merging in LDS, so the call is one launch without a
-//   prologue over the batch; a batch too small to fill the CUs cuts its long
-//   items into chunks of equal length, merged by a second launch.
+// * Short contexts and small batches take another kernel (item_split in
+//   attention_route.h says which): a workgroup per (request, KV head), its four
+//   waves sharing the item's spans and merging in LDS, so the call is one launch
+//   without a prologue over the batch; a batch too small to fill the CUs cuts its
+//   long items into chunks of equal length, merged by a second launch.
 // * Masked tokens (past a query's position, past L_r, or in a block whose id
 //   is out of range) are removed by selection: scores become -inf and V
 //   elements past L_r are zeroed, so NaN-filled unused slots never leak.
+#include "attention_route.h"
 #include "nsd_internal.h"
 
 #include <math.h>
@@ -1205,7 +1206,7 @@ constexpr int kItemBlocks = 2;   // blocks per step
 __host__ __device__ constexpr bool item_shares_q(int d, int mt) { return d * mt == 384; }
 
 __host__ __device__ constexpr int item_waves_per_simd(int d, int mt) {
-  return d * mt <= 384 ? 2 : 1;
+  return two_waves_per_simd(d * mt) ? 2 : 1;
 }
 
 constexpr int kItemWaves = 4;
@@ -1793,48 +1794,6 @@ void launch_d(const Params& p, int mt, int bs, size_t lds_bytes, hipStream_t str
   }
 }
 
-// How a batch runs: the most chunks the item kernel cuts an item into (1: none
-// is cut), or 0 for the wave-split kernel.  items = requests x KV heads, b =
-// K/V bytes of the longest context the call can hold per item, two_waves:
-// the tile keeps two waves per SIMD, slots: partial slots of the workspace.
-//
-// The item kernel has no prologue over the batch, no merge launch when nothing
-// is cut, and the hardware hands its workgroups to free CUs; but an item's
-// time is bound by one CU (about 49 bytes per ns), and the
-// fused pass loses the order that keeps the writes together.  Lines measured
-// on MI355X (us, wave-split kernel -> item kernel; 32/8 heads, D 128, K = 4
-// unless said; items x longest context, lengths uniform from a quarter of it):
-//   whole items, read only: 192 x 1024 33 -> 18, 256 x 2048 43 -> 35, 256 x
-//     4096 62 -> 59 (384 x 4096 89 -> 94, 512 x 4096 118 -> 120), 512 x 2048
-//     67 -> 61 (1024 x 2048, 16/8 heads, K = 0: 107 -> 109), 1024 x 1024
-//     70 -> 62, 4096 x 512 (16/8, K = 0) 118 -> 108;
-//   cut items, read only: 8 x 32001 39 -> 31, 8 x 4096 21 -> 14, 64 x 4096
-//     32 -> 27, 128 x 4096 45 -> 41, 64 x 16000 even (128 x 16000 124 -> 133);
-//   whole items, fused, 30 % arriving: 32 x 256 30 -> 9, 256 x 1024 49 -> 31,
-//     256 x 2048 61 -> 51 (512 x 2048 98 -> 102), 512 x 1024 66 -> 56 (2048 x
-//     1024 179 -> 186), 2048 x 512 108 -> 97;
-//   cut items, fused: 32 x 1024 35 -> 13, 32 x 4096 37 -> 20, 64 x 4096
-//     44 -> 33, 128 x 4096 60 -> 57 (128 x 16000 180 -> 214);
-//   64 rows at head_dim 128 (one wave per SIMD): 512 x 1024 57 -> 52 (2048 x
-//     1024 173 -> 179, 64 x 4096 41 -> 56).
-int item_split(int64_t items, int64_t b, bool two_waves, bool fuse, int cus, int64_t slots) {
-  constexpr int64_t KB = 1024, MB = 1024 * KB;
-  const int64_t total = items * b;
-  const int few = two_waves ? cus / 2 : cus / 16;   // so few items leave CUs idle: cut them
-  if (items <= few && b > (fuse && two_waves ? 256 : 512) * KB) {
-    const bool cut = !two_waves ? total <= 64 * MB
-                     : fuse     ? b <= 2 * MB || total <= 150 * MB
-                                : total <= 400 * MB;
-    if (!cut) return 0;
-    // twice the workgroups aimed at: the longest context may take two shares
-    return (int)std::max<int64_t>(1, std::min(slots / items, (4 * cus + items - 1) / items));
-  }
-  if (!two_waves) return b <= 512 * KB && items <= 2 * cus;
-  if (fuse)
-    return b <= 256 * KB || (b <= 512 * KB && items <= 2 * cus) || (b <= MB && items <= cus);
-  return b <= 512 * KB || (b <= MB && items <= 2 * cus) || (b <= 2 * MB && items <= cus);
-}
-
 // Shared by both entry points: validation, workspace carving, launch.
 nsd_status run(const char* fn, bool fuse, const void* q, const void* k_cache,
                const void* v_cache, void* k_dst, void* v_dst, int64_t num_blocks,
@@ -1935,8 +1894,8 @@ nsd_status run(const char* fn, bool fuse, const void* q, const void* k_cache,
   p.split_groups = 2 * ki.cus;
   p.split = g_waves_override.load(std::memory_order_relaxed) > 0
                 ? 0
-                : item_split((int64_t)bs * num_kv_heads, most * head_dim * 4, head_dim * pl.mt <= 384,
-                             fuse, ki.cus, 4 * (int64_t)pl.num_waves);
+                : item_split((int64_t)bs * num_kv_heads, most * head_dim * 4, head_dim, pl.mt, fuse,
+                             ki.cus, 4 * (int64_t)pl.num_waves);
   p.out_off = (int32_t)pre_bytes;
   p.out_cap = (int32_t)per_wave;
   const size_t lds_bytes = pre_bytes + 4 * per_wave;

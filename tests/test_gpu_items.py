@@ -92,3 +92,20 @@ def test_row_tiles(device, hq, hkv, d, fused):
             out = nsd.verify_attention(lay.q, lay.k_pool, lay.v_pool, table, *args)
         torch.cuda.synchronize()
         check_attention(meta, lay, out, range(len(n)))
+
+
+def test_more_items_than_a_grid_takes(device):
+    """8192 requests of 2049 KV heads: a workgroup per item would be 2^32 threads, so the wave
+    split takes them.  One token per context, so each output row is that token's V."""
+    bs, hkv, d = 8192, 2049, 64
+    gen = torch.Generator(device=device).manual_seed(5)
+    k = torch.randn((2, hkv, d // 8, 16, 8), generator=gen, device=device).bfloat16()
+    v = torch.randn((2, hkv, d, 16), generator=gen, device=device).bfloat16()
+    q = torch.randn((bs, hkv, d), generator=gen, device=device).bfloat16()
+    table = (torch.arange(bs, device=device, dtype=torch.int32) % 2)[:, None].contiguous()
+    out = nsd.verify_attention(q, k, v, table,
+                               torch.ones(bs, dtype=torch.int32, device=device),
+                               torch.arange(bs + 1, dtype=torch.int32, device=device), 1, 1)
+    torch.cuda.synchronize()
+    for r in (0, 1):
+        assert torch.equal(out[r::2], v[r, :, :, 0].expand(bs // 2, hkv, d))
