@@ -149,6 +149,7 @@ struct Params {
   int32_t split;           // item kernel: most chunks an item is cut into (1: none is cut)
   int32_t split_groups;    // item kernel: workgroups the cut aims at
   int32_t merge_waves;     // bound of the ranges per segment the waves take, from the longest context
+  int32_t by_item;         // cut items are merged by item (else by range), and the waves are finer
   int32_t out_off;         // dynamic LDS: byte offset of the output buffers
   int32_t out_cap;         // bytes of each wave's output buffer
   int32_t w_even;          // relative range length of waves on even XCDs
@@ -783,19 +784,23 @@ struct Ranges {
     const int64_t k = q % 8;
     return (q / 8) * 4 * (we + wo) + (k < 4 ? k * we : 4 * we + (k - 4) * wo);
   }
-  __device__ int64_t begin(int64_t rid) const { return T * weight_before(rid) / total; }
-  __device__ int64_t end(int64_t rid) const { return T * weight_before(rid + 1) / total; }
+  // floor(x / y) by an fp64 quotient: for quotients below 2^52 it is off by at most
+  // one, which the remainder shows (a 64-bit integer division is over a hundred
+  // instructions, and the merge makes two for a part)
+  __device__ static int64_t floor_div(int64_t x, int64_t y) {
+    const int64_t g = (int64_t)((double)x / (double)y);
+    const int64_t rest = x - g * y;
+    return g + (rest < 0 ? -1 : (rest >= y ? 1 : 0));
+  }
+  __device__ int64_t begin(int64_t rid) const { return floor_div(T * weight_before(rid), total); }
+  __device__ int64_t end(int64_t rid) const {
+    return floor_div(T * weight_before(rid + 1), total);
+  }
   // range holding span s: the last q with begin(q) <= s, i.e. the last q
   // with weight_before(q) <= G = floor(((s + 1) * total - 1) / T), found by
-  // inverting the piecewise-linear weight_before
+  // inverting the piecewise-linear weight_before (G is below the total weight, 2^27)
   __device__ int64_t of(int64_t s) const {
-    // floor(x / T) by an fp64 quotient: the quotient stays below 2^27 (the
-    // total weight), so it is off by at most one, which the remainder shows
-    // (a 64-bit integer division is over a hundred instructions)
-    const int64_t x = (s + 1) * total - 1;
-    int64_t G = (int64_t)((double)x / (double)T);
-    const int64_t rest = x - G * T;
-    G += rest < 0 ? -1 : (rest >= T ? 1 : 0);
+    const int64_t G = floor_div((s + 1) * total - 1, T);
     const uint32_t blk = (uint32_t)(4 * (we + wo));
     const uint32_t full = (uint32_t)G / blk;
     const uint32_t rem = (uint32_t)G - full * blk;
@@ -811,12 +816,15 @@ struct Ranges {
 // spread over every resident wave cuts each item into one-span parts whose
 // merge costs more than the streaming (a one-request round ran in 65 us on
 // 1024 waves and 29 us on 64); too few waves leave HBM idle.  Measured on
-// MI355X with the merge by item: the separate attention is best at about one
-// wave per 8 blocks (8 x 4096 tokens, 32/8 heads, 26.0 us at one per 20, 21.7
+// MI355X with the merge by item (fine): the separate attention is best at about
+// one wave per 8 blocks (8 x 4096 tokens, 32/8 heads, 26.0 us at one per 20, 21.7
 // at one per 8), the fused pass at B / (6 + B / 1000) waves (4 requests of
 // 4000-16000 tokens 74 us at B / (15 + B / 1000), 58 so; 8 requests 106 and
-// 97), and with every resident wave once that passes 7/8 of them.  Every
-// kernel derives the same count from the segments' spans.
+// 97), and with every resident wave once that passes 7/8 of them.  The merge by
+// range walks an item's parts with one wave, so there the counts are coarser:
+// one wave per 20 blocks, B / (15 + B / 1000) (512 requests, one of 4096 tokens
+// among 16-64, 4/2 heads, head_dim 64: 34 us with the finer counts, 31 so, fused
+// 47 and 39).  Every kernel derives the same count from the segments' spans.
 constexpr int kMinWaves = 64;
 constexpr int kMinCopyWaves = 64;   // surplus waves that take over the fused pass's pool writes
 
@@ -827,8 +835,9 @@ __device__ inline int64_t segment_blocks(int64_t ta, int64_t tb) {
 
 // Non-decreasing in B (the host bounds the count by the longest context).
 template <bool FUSE>
-__host__ __device__ inline int64_t waves_for(int64_t B, int64_t W) {
-  int64_t want = FUSE ? B * 1000 / (6000 + B) : (B + 7) / 8;
+__host__ __device__ inline int64_t waves_for(int64_t B, int64_t W, bool fine) {
+  const int64_t per = fine ? (FUSE ? 6 : 8) : (FUSE ? 15 : 20);   // blocks a wave takes
+  int64_t want = FUSE ? B * 1000 / (per * 1000 + B) : (B + per - 1) / per;
   if (FUSE && 8 * want > 7 * W) want = W;
   want = (want + 3) / 4 * 4;
   if (want < kMinWaves) want = kMinWaves;
@@ -1139,7 +1148,7 @@ void verify_attention_kernel(Params p, const int32_t* __restrict__ block_table,
                           p.num_waves, lane);
     return;
   }
-  const int64_t W = waves_for<FUSE>(segment_blocks<D, MT>(ta, tb), p.num_waves);
+  const int64_t W = waves_for<FUSE>(segment_blocks<D, MT>(ta, tb), p.num_waves, p.by_item);
   if (blockIdx.x == 0 && tid == 0)
     *(uint4*)p.head = make_uint4(s_pre[n_res], s_pre[p.bs] - s_pre[n_res], (uint32_t)W, 0u);
   // a batch too small for every resident wave: the surplus waves write the
@@ -1454,6 +1463,7 @@ __device__ inline void merge_into(MergeAcc& a, float m, float l, float scale,
 }
 
 constexpr int kMergeMaxSplit = 16;   // waves that share the parts of one row group
+constexpr int kMergeAhead = 4;       // parts a wave loads before it merges the first
 
 // Merge the partials of every cut item, in order (deterministic, no atomics).
 // A wave owns a group of 64 / (D / 8) rows, a lane 8 columns of a row (one
@@ -1546,7 +1556,7 @@ __global__ __launch_bounds__(1024) void combine_kernel(Params p) {
   const int mld = min(m, rows - 1);      // loads clamped into the item's rows
   MergeAcc acc;
   merge_init(acc);
-  constexpr int kAhead = 4;              // parts loaded before the first is merged
+  constexpr int kAhead = kMergeAhead;
   for (int64_t q0 = ra + s0; q0 <= rb; q0 += (int64_t)split * kAhead) {
     float2 ml[kAhead];
     u32x4 w[kAhead];
@@ -1579,14 +1589,17 @@ __global__ __launch_bounds__(1024) void combine_kernel(Params p) {
   if constexpr (ITEM) {
     // the waves' merges meet in LDS, in wave order
     extern __shared__ float s_part[];      // [waves][10][64]
-    float* mine = s_part + wave * 640 + lane;
+    const int used = (int)min((int64_t)waves, rb - ra + 1);   // (the other waves had no part)
+    if (wave < used) {
+      float* mine = s_part + wave * 640 + lane;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) mine[i * 64] = acc.o[i];
-    mine[512] = acc.m;
-    mine[576] = acc.l;
+      for (int i = 0; i < 8; ++i) mine[i * 64] = acc.o[i];
+      mine[512] = acc.m;
+      mine[576] = acc.l;
+    }
     __syncthreads();
     if (wave != 0) return;
-    for (int k = 1; k < waves; ++k) {
+    for (int k = 1; k < used; ++k) {
       const float* from = s_part + k * 640 + lane;
       float o[8];
 #pragma unroll
@@ -1749,11 +1762,17 @@ int row_groups(const Params& p) {
   return (p.group * p.max_q + 64 / (D / 8) - 1) / (64 / (D / 8));
 }
 
-// The merge by item, with about one wave for every two of an item's parts.
+// The merge by item, with about one wave for every two of an item's parts, but no
+// more than four rounds of loads for the item of most parts, the longest context
+// (32768 tokens among 16-64, 256 items of head_dim 64: 104 us with the waves the
+// mean item needs, 39 so).
 template <int D, int MT, int MODE>
-void launch_merge(const Params& p, uint32_t items, int parts, hipStream_t stream) {
+void launch_merge(const Params& p, uint32_t items, int parts, int most_parts,
+                  hipStream_t stream) {
   int split = 1;
-  while (split < kMergeMaxSplit && 2 * split < parts) split *= 2;
+  while (split < kMergeMaxSplit &&
+         (2 * split < parts || 4 * kMergeAhead * split < most_parts))
+    split *= 2;
   hipLaunchKernelGGL((combine_kernel<D, MT, MODE>), dim3(items, row_groups<D>(p)),
                      dim3(64 * split), (size_t)split * 640 * sizeof(float), stream, p);
 }
@@ -1766,22 +1785,25 @@ void launch(const Params& p, int bs, size_t lds_bytes, hipStream_t stream) {
                        dim3(kItemWaves * 64), 0, stream, p, p.block_table, p.stage_table,
                        p.seq_lens, p.q_indptr);
     if (p.split == 1) return;
-    launch_merge<D, MT, kByChunk>(p, items, p.split, stream);
+    launch_merge<D, MT, kByChunk>(p, items, p.split, p.split, stream);
     return;
   }
   hipLaunchKernelGGL((verify_attention_kernel<D, MT, FUSE>), dim3(p.num_waves / 4), dim3(256),
                      lds_bytes, stream, p, p.block_table, p.stage_table, p.seq_lens,
                      p.q_indptr);
-  // by item where the ranges are at least twice the items (every item is cut,
-  // so every workgroup has work: 24 requests x 8 KV heads 6.0 us by item, 7.3
-  // by range; 32 requests fused 6.2 against 8.4 us); by range otherwise (most
-  // items of a large batch are whole)
-  const int64_t ranges = (int64_t)(FUSE ? 2 : 1) * p.merge_waves;
-  if (2 * (int64_t)items <= ranges)
-    launch_merge<D, MT, kByItem>(p, items, (int)(ranges / items), stream);
-  else
-    hipLaunchKernelGGL((combine_kernel<D, MT, kByRange>), dim3((uint32_t)ranges),
+  const uint32_t ranges = (uint32_t)(FUSE ? 2 : 1) * p.merge_waves;
+  if (p.by_item) {
+    // the longest context's blocks over the fewest a wave takes; its heads share
+    // the ranges
+    const int64_t blocks = std::min<int64_t>(((int64_t)p.max_seq_len + kBlock - 1) / kBlock,
+                                             p.max_blocks_per_seq);
+    const int most_parts =
+        (int)std::min<int64_t>(p.merge_waves / p.num_kv_heads, blocks / (FUSE ? 6 : 8));
+    launch_merge<D, MT, kByItem>(p, items, (int)(ranges / items), most_parts, stream);
+  } else {
+    hipLaunchKernelGGL((combine_kernel<D, MT, kByRange>), dim3(ranges),
                        dim3(64 * row_groups<D>(p)), 0, stream, p);
+  }
 }
 
 template <int D, bool FUSE>
@@ -1881,8 +1903,18 @@ nsd_status run(const char* fn, bool fuse, const void* q, const void* k_cache,
   // work, so none is launched
   const int64_t most = std::min<int64_t>(max_seq_len, (int64_t)max_blocks_per_seq * kBlock);
   const int64_t blocks = (int64_t)bs * num_kv_heads * std::max<int64_t>(1, (most + 63) / 64) * 4;
-  p.merge_waves = (int32_t)(fuse ? waves_for<true>(blocks, pl.num_waves)
-                                 : waves_for<false>(blocks, pl.num_waves));
+  // merged by item where the ranges are at least twice the items (every item is
+  // cut, so every workgroup of the merge has work: 24 requests x 8 KV heads 6.0 us
+  // by item, 7.3 by range; 32 requests fused 6.2 against 8.4 us, but 128 requests
+  // fused, one of 1024 tokens among 16-64, 57.3 us by item, 54.6 by range); by range
+  // otherwise (most items of a large batch are whole)
+  const int64_t items = (int64_t)bs * num_kv_heads;
+  auto bound = [&](bool fine) {
+    return fuse ? waves_for<true>(blocks, pl.num_waves, fine)
+                : waves_for<false>(blocks, pl.num_waves, fine);
+  };
+  p.by_item = fuse ? items < bound(true) : 2 * items <= bound(true);
+  p.merge_waves = (int32_t)bound(p.by_item);
   p.num_waves = fuse ? pl.num_waves : p.merge_waves;
   // measured HBM streaming speed of odd-XCD waves relative to even ones, in
   // the read-only resident segment and in the arriving segment (which also
@@ -1894,8 +1926,8 @@ nsd_status run(const char* fn, bool fuse, const void* q, const void* k_cache,
   p.split_groups = 2 * ki.cus;
   p.split = g_waves_override.load(std::memory_order_relaxed) > 0
                 ? 0
-                : item_split((int64_t)bs * num_kv_heads, most * head_dim * 4, head_dim, pl.mt, fuse,
-                             ki.cus, 4 * (int64_t)pl.num_waves);
+                : item_split(items, most * head_dim * 4, head_dim, pl.mt, fuse, ki.cus,
+                             4 * (int64_t)pl.num_waves);
   p.out_off = (int32_t)pre_bytes;
   p.out_cap = (int32_t)per_wave;
   const size_t lds_bytes = pre_bytes + 4 * per_wave;

@@ -44,3 +44,37 @@ def test_merge(device, case, fused):
                                        i32(meta.block_table, device), *args)
     torch.cuda.synchronize()
     check_attention(meta, lay, out, range(bs))
+
+
+SKEWED = [
+    # (Hq, Hkv, D, one long context, requests, rows K + 1)
+    (4, 2, 64, 9000, 130, 5),        # by item: the long items hold ~256 parts, spans as few as waves
+    (16, 1, 128, 5000, 200, 1),      # by item, one KV head
+    (8, 2, 128, 9000, 300, 4),       # by range where waves are few (not fused)
+    (8, 8, 64, 5000, 128, 2),        # 1024 items: by range, fused at the line too
+]
+
+
+@pytest.mark.parametrize("case", range(len(SKEWED)))
+@pytest.mark.parametrize("fused", [False, True])
+def test_merge_skewed(device, case, fused):
+    """One context far longer than the others: its items hold most of the parts."""
+    hq, hkv, d, longest, bs, rows = SKEWED[case]
+    rng = np.random.default_rng(case)
+    lens = rng.integers(16, 65, bs)
+    lens[bs // 3] = longest
+    cfg = custom_config(seed=950 + case, bs=bs, num_q_heads=hq, num_kv_heads=hkv, head_dim=d,
+                        vocab=0, n_arriving=0, pool_blocks=None)
+    meta = make_meta(cfg, seq_lens=lens, depth=np.full(bs, rows - 1),
+                     arriving=(np.arange(bs) % 3 == 0) & fused)
+    lay = make_layer(cfg, meta, 0, device)
+    args = (i32(meta.seq_lens, device), i32(meta.q_indptr, device), meta.max_q, meta.max_seq_len)
+    kp, vp = lay.k_pool.clone(), lay.v_pool.clone()
+    if fused:
+        out = nsd.gather_verify_attention(
+            lay.q, kp, vp, lay.k_stage, lay.v_stage, i32(meta.block_table, device),
+            i32(meta.stage_table, device), *args)
+    else:
+        out = nsd.verify_attention(lay.q, kp, vp, i32(meta.block_table, device), *args)
+    torch.cuda.synchronize()
+    check_attention(meta, lay, out, range(bs))
