@@ -2,6 +2,7 @@
 (in-tree, no JIT cache)."""
 import importlib.util
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -47,9 +48,18 @@ def _link(objs, path):
 
 
 def _build_binding():
+    """The marshalling module; without a host compiler or torch's headers none is built (the
+    package then submits through ctypes), and one of other sources does not stay."""
     torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+    cxx = os.environ.get("CXX", "g++")
+    headers = os.path.join(torch_dir, "include", "torch", "csrc", "autograd", "python_variable.h")
+    if not shutil.which(cxx) or not os.path.exists(headers):
+        print(f"no {BINDING_SOURCE} built: {cxx} or torch's headers are missing", file=sys.stderr)
+        if os.path.exists(BINDING_PATH):
+            os.remove(BINDING_PATH)
+        return
     tmp = BINDING_PATH + ".tmp"
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-I{os.path.join(ROOT, 'include')}",
            "-isystem", os.path.join(torch_dir, "include"),
            "-isystem", os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
