@@ -47,6 +47,19 @@ def _link(objs, path):
     os.replace(tmp, path)
 
 
+def _rocm_include():
+    """The include folder with HIP's headers: ROCM_PATH's, the one beside HIPCC (a bare name is
+    looked up in PATH, links are followed), or the default installation's."""
+    roots = [os.environ.get("ROCM_PATH")]
+    hipcc = shutil.which(HIPCC)
+    for path in (hipcc, hipcc and os.path.realpath(hipcc)):
+        roots.append(path and os.path.dirname(os.path.dirname(path)))
+    for root in filter(None, roots + ["/opt/rocm"]):
+        if os.path.exists(os.path.join(root, "include", "hip", "hip_runtime_api.h")):
+            return os.path.join(root, "include")
+    raise RuntimeError(f"HIP's headers are not beside {HIPCC} nor under ROCM_PATH")
+
+
 def _build_binding():
     """The marshalling module; without a host compiler or torch's headers none is built (the
     package then submits through ctypes), and one of other sources does not stay."""
@@ -63,7 +76,7 @@ def _build_binding():
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-I{os.path.join(ROOT, 'include')}",
            "-isystem", os.path.join(torch_dir, "include"),
            "-isystem", os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
-           "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
+           "-isystem", _rocm_include(),
            f"-I{sysconfig.get_paths()['include']}", os.path.join(CSRC, BINDING_SOURCE),
            "-o", tmp, f"-L{os.path.join(torch_dir, 'lib')}", "-ltorch_python", "-ltorch",
            "-ltorch_cpu", "-lc10", "-lc10_hip"]

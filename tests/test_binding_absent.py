@@ -69,3 +69,21 @@ def test_build_without_a_host_compiler(tmp_path, monkeypatch, capsys):
     monkeypatch.setenv("CXX", str(tmp_path / "none"))
     build._build_binding()
     assert not path.exists() and "no torch_binding.cpp built" in capsys.readouterr().err
+
+
+@pytest.mark.parametrize("how", ["path", "name", "link"])
+def test_hip_headers_are_found(how, tmp_path, monkeypatch):
+    """HIPCC as a path, as a name to look up in PATH, and behind a link."""
+    (tmp_path / "rocm" / "bin").mkdir(parents=True)
+    (tmp_path / "rocm" / "include" / "hip").mkdir(parents=True)
+    (tmp_path / "rocm" / "include" / "hip" / "hip_runtime_api.h").write_text("")
+    hipcc = tmp_path / "rocm" / "bin" / "hipcc"
+    hipcc.write_text("")
+    hipcc.chmod(0o755)
+    (tmp_path / "link").mkdir()
+    (tmp_path / "link" / "hipcc").symlink_to(hipcc)
+    at = {"path": str(hipcc), "name": "hipcc", "link": str(tmp_path / "link" / "hipcc")}[how]
+    monkeypatch.delenv("ROCM_PATH", raising=False)
+    monkeypatch.setenv("PATH", str(hipcc.parent), prepend=os.pathsep)
+    monkeypatch.setattr(build, "HIPCC", at)
+    assert build._rocm_include() == str(tmp_path / "rocm" / "include")
