@@ -198,6 +198,14 @@ static nsd_status append_layers(const char* fn, const Bank* banks, int32_t n_lay
   if (bs < 0 || total_q < 0 || num_kv_heads < 1 || num_kv_heads > 65535 || bs > 65535 ||
       max_blocks_per_seq < 1 || banks[0].num_blocks < 0 || banks[1].num_blocks < 0 || n_layers < 0)
     return fail(NSD_ERR_SHAPE, "%s: bad sizes", fn);
+  // planes stacked over layers are addressed with 64-bit byte offsets
+  for (int b = 0; b < 2; ++b) {
+    int64_t bytes;
+    if (n_layers > 1 &&
+        (__builtin_mul_overflow(banks[b].num_blocks, (int64_t)num_kv_heads * head_dim * 32, &bytes) ||
+         __builtin_mul_overflow(bytes, (int64_t)n_layers, &bytes)))
+      return fail(NSD_ERR_SHAPE, "%s: planes of more than 2^63-1 bytes", fn);
+  }
   if (bs == 0 || total_q == 0 || n_layers == 0) return NSD_OK;
   if (!banks[0].k || !banks[0].v || !k_new || !v_new || !banks[0].table || !seq_lens ||
       !q_indptr || (second && (!banks[1].k || !banks[1].v)))

@@ -91,7 +91,8 @@ def fuzz_entry_points(rng, n_iter):
     lib = nsd.lib()
     fns = ["nsd_kv_gather", "nsd_verify_attention_workspace_size", "nsd_verify_attention",
            "nsd_gather_verify_attention", "nsd_spec_accept_workspace_size", "nsd_spec_accept",
-           "nsd_sample", "nsd_kv_append", "nsd_commit_lengths"]
+           "nsd_sample", "nsd_kv_append", "nsd_commit_lengths", "nsd_kv_append_layers",
+           "nsd_spec_accept_commit", "nsd_sample_steps"]
     i32 = [0, 1, 2, 3, 4, 7, 8, 16, 63, 64, 128, 256, 1000, 4096, 65535, 151936, 1 << 19, 2**30,
            -1, -16, I32_MAX, -2**31]
     i64 = i32 + [2**33, 2**40, 2**62, 2**63 - 1, -2**63]
@@ -110,8 +111,21 @@ def fuzz_entry_points(rng, n_iter):
         raise TypeError(t)
 
     for it in range(n_iter):
-        f = getattr(lib, fns[it % len(fns)])
-        f(*[arg(t) for t in f.argtypes])
+        name = fns[it % len(fns)]
+        f = getattr(lib, name)
+        args = [arg(t) for t in f.argtypes]
+        if name == "nsd_kv_append_layers":
+            # k_new and v_new are host arrays of n_layers pointers, which host code does read
+            args[8] = int(rng.choice([0, 1, 2, 31, 32, 33, 64, 65, 200, -1, -2**31]))
+            rows = [(ctypes.c_void_p * 200)(*[arg(ctypes.c_void_p) if rng.random() < 0.02
+                                              else fake[0]] * 200) for _ in range(2)]
+            args[9:11] = [None if rng.random() < 0.1 else ctypes.addressof(r) for r in rows]
+            if rng.random() < 0.7:      # past the small checks: the sizes of the planes remain
+                args[0:2], args[4:6] = fake[:2], fake[:2]
+                args[3], args[7], args[12], args[13] = fake[:4]
+                args[11], args[14], args[15], args[16] = 4, 4, 8, int(rng.choice([1, 8, 65535]))
+                args[17], args[18] = 16, int(rng.choice([64, 128]))
+        f(*args)
 
 
 if __name__ == "__main__":

@@ -160,6 +160,60 @@ def test_append_commit_alias_validation(lib):
     assert lib.nsd_host_alias(None, ctypes.byref(out)) == 1
 
 
+def test_append_layers_validation(lib):
+    f = lib.nsd_kv_append_layers
+    fake = 16    # a device address, never dereferenced
+    rows = (ctypes.c_void_p * 40)(*[fake] * 40)
+    at = ctypes.addressof(rows)
+    args = lambda **kw: [kw.get(k, v) for k, v in [
+        ("k", fake), ("v", fake), ("nb", 8), ("bt", fake), ("ks", fake), ("vs", fake), ("ns", 4),
+        ("st", fake), ("layers", 40), ("kn", at), ("vn", at), ("mbps", 4), ("sl", fake),
+        ("qi", fake), ("bs", 2), ("tq", 8), ("hkv", 2), ("blk", 16), ("d", 64), ("stream", None)]]
+    assert f(*args(blk=8)) == 3 and f(*args(d=96)) == 3
+    assert f(*args(layers=-1)) == 2 and f(*args(mbps=0)) == 2 and f(*args(ns=-1)) == 2
+    assert f(*args(layers=0, kn=None, vn=None)) == 0 and f(*args(bs=0, k=None)) == 0
+    for name in ("k", "v", "bt", "ks", "vs", "kn", "vn", "sl", "qi"):
+        assert f(*args(**{name: None})) == 1, name
+    for name in ("k", "v", "ks", "vs"):
+        assert f(*args(**{name: 24})) == 2, name
+        assert b"16-byte aligned" in lib.nsd_last_error()
+    rows[33] = None                                   # a layer past the first launch's
+    assert f(*args()) == 1
+    rows[33] = fake
+    # planes whose stacked size passes 2^63 bytes, in either bank, are refused
+    for name in ("nb", "ns"):
+        assert f(*args(**{name: 2**62})) == 2, name
+        assert b"2^63" in lib.nsd_last_error()
+
+
+def test_accept_commit_and_sample_steps_validation(lib):
+    z = (None, 0, None)
+    f = lib.nsd_spec_accept_commit
+    assert f(None, None, None, None, None, 0, 1000, 4, None, None, None, None, *z) == 0
+    fake = 1 << 20
+    good = [fake] * 5 + [4, 1000, 4] + [fake] * 4 + [fake, 16, None]
+    for at in (0, 1, 2, 3, 4, 8, 9, 10, 11):
+        bad = list(good)
+        bad[at] = None
+        assert f(*bad) == 1, at
+    assert f(*good) == 4 and b"workspace" in lib.nsd_last_error()
+    for at, value, status in ((6, 1001, 3), (7, 64, 3), (5, -1, 2), (0, fake + 8, 2)):
+        bad = list(good)
+        bad[at] = value
+        assert f(*bad) == status, (at, value)
+    f = lib.nsd_sample_steps
+    assert f(None, 4000, None, 4, 4, 1001, None, 4, *z) == 3                # vocab % 4
+    assert f(None, 3996, None, 4, 4, 1000, None, 4, *z) == 2                # row_stride < steps rows
+    assert f(None, 4002, None, 4, 4, 1000, None, 4, *z) == 2                # row_stride % 4
+    assert f(None, 4000, None, 4, 4, 1000, None, 3, *z) == 2                # out_stride < steps
+    assert f(None, 4000, None, 4, 0, 1000, None, 4, *z) == 2                # no step
+    assert f(None, 2**62, None, 2**30, 2**30, 1000, None, 2**30, *z) == 2   # rows past 2^31
+    assert f(None, 4000, None, 0, 4, 1000, None, 4, *z) == 0
+    assert f(None, 4000, None, 4, 4, 1000, None, 4, *z) == 1
+    assert f(8, 4000, 8, 4, 4, 1000, 8, 4, *z) == 2 and b"aligned" in lib.nsd_last_error()
+    assert f(16, 4000, 16, 4, 4, 1000, 16, 4, *z) == 4                      # no workspace
+
+
 def test_probe_library_exports_and_validates():
     """The bandwidth-probe library (measurement only) exports what its header
     declares and refuses bad arguments before any launch."""
