@@ -472,6 +472,15 @@ PyObject* py_commit_lengths(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
+// References to the tensors inside a call's tuples and lists: the call runs without
+// the interpreter lock, and a list's owner may change it meanwhile.
+using Held = std::vector<Tensor>;
+
+const Tensor& held(Held& h, const Tensor& t) {
+  h.push_back(t);
+  return t;
+}
+
 // A tuple or list of n items, or NotHere.
 PyObject** items_of(PyObject* o, Py_ssize_t n) {
   if (!PyTuple_CheckExact(o) && !PyList_CheckExact(o)) throw NotHere();
@@ -513,6 +522,7 @@ PyObject* py_verify_round(PyObject*, PyObject* const* a, Py_ssize_t n) {
     } else {
       g = gather_args(ks, vs, k, v, a[4], a[5]);
     }
+    Held h;
     std::vector<const void*> k_new, v_new;
     const int32_t *pool_table = b.table, *stage_rows = nullptr;
     if (a[17] != Py_None) {
@@ -520,7 +530,7 @@ PyObject* py_verify_round(PyObject*, PyObject* const* a, Py_ssize_t n) {
       need(PySequence_Fast_GET_SIZE(a[17]) >= layers);
       for (int64_t l = 0; l < layers; ++l) {
         PyObject** kv = items_of(rows[l], 2);
-        const Tensor &kn = bf16(kv[0]), &vn = bf16(kv[1]);
+        const Tensor &kn = held(h, bf16(kv[0])), &vn = held(h, bf16(kv[1]));
         need(kn.dim() == 3 && kn.size(0) == total && kn.size(1) == b.hkv && kn.size(2) == b.d &&
              vn.sizes() == kn.sizes());
         k_new.push_back(kn.data_ptr());
@@ -528,7 +538,7 @@ PyObject* py_verify_round(PyObject*, PyObject* const* a, Py_ssize_t n) {
       }
       if (fused) {
         PyObject** tables = items_of(a[19], 2);
-        const Tensor &pt = i32(tables[0]), &sr = i32(tables[1]);
+        const Tensor &pt = held(h, i32(tables[0])), &sr = held(h, i32(tables[1]));
         need(pt.dim() == 2 && pt.size(0) == b.bs && pt.size(1) == b.width &&
              sr.sizes() == pt.sizes());
         pool_table = pt.data_ptr<int32_t>();
@@ -542,6 +552,8 @@ PyObject* py_verify_round(PyObject*, PyObject* const* a, Py_ssize_t n) {
       PyObject** in = items_of(a[12], 5);
       accept_args(s, in[0], in[1], in[2], in[3], i32(a[9]), in[4], Py_None, Py_None, a[20]);
       need(any_tensor(in[0]).device() == q.device());
+      for (int i : {0, 1, 2, 3})
+        if (s.max_k > 0 || i % 3 == 0) held(h, any_tensor(in[i]));   // (no draft rows without K)
       if (a[18] != Py_None) {
         const Tensor& c = i32(a[18]);
         need(c.numel() == b.bs);
@@ -615,13 +627,14 @@ PyObject* py_draft_stage(PyObject*, PyObject* const* a, Py_ssize_t n) {
     b.ws_bytes = ws.numel();
     b.stream = stream_of(q);
     Planes stage{nullptr, nullptr, 0, 0};
+    Held h;
     const int32_t *pool_table = nullptr, *stage_rows = nullptr;
     const bool fused = a[13] != Py_None;
     if (fused) {
       stage_table(b, a[13]);
       stage = planes(bf16(a[11]), bf16(a[12]), false, b.hkv, b.d);
       PyObject** tables = items_of(a[18], 2);
-      const Tensor &pt = i32(tables[0]), &sr = i32(tables[1]);
+      const Tensor &pt = held(h, i32(tables[0])), &sr = held(h, i32(tables[1]));
       need(pt.dim() == 2 && pt.size(0) == b.bs && pt.size(1) == b.width &&
            sr.sizes() == pt.sizes());
       pool_table = pt.data_ptr<int32_t>();

@@ -1,6 +1,8 @@
 """The native marshalling against the Python one: a tensor subclass is not taken
 natively, so the same calls with one go through ctypes; outputs are identical,
 with and without the caller's buffers, and a wrong argument raises the same."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -151,3 +153,37 @@ def test_faults_raise_the_same(device):
     with pytest.raises(nsd.NsdError) as e:
         nsd.verify_attention(*good, workspace=torch.empty(16, dtype=torch.uint8, device=device))
     assert e.value.status == 4 and "workspace" in str(e.value)
+
+
+def test_a_list_changed_during_the_call(device):
+    """The native round runs without the interpreter lock; rows taken out of the caller's list
+    meanwhile stay alive until it has submitted its last launch."""
+    cfg, meta, (k, v, ks, vs, q) = setup(device)
+    ws = nsd.new_workspace(nsd.verify_attention_workspace_size(
+        cfg.bs, 8, 2, 128, meta.max_q, meta.max_seq_len), device)
+    row = lambda: torch.zeros((meta.total_q, 2, 128), dtype=torch.bfloat16, device=device)
+    rows = [[row(), row()] for _ in range(2)]
+    seen = []
+    res, args = nsd._SIGS["nsd_kv_append_layers"]
+
+    def append(*a):      # in the entry point's place: another thread empties the list
+        before = torch.cuda.memory_allocated()
+        rows.clear()
+        seen.append(torch.cuda.memory_allocated() - before)
+        return 0
+
+    callback = ctypes.CFUNCTYPE(res, *args)(append)
+    at = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    real = [at(getattr(nsd.lib(), f)) for f in nsd._BOUND]
+    native = nsd._native()
+    try:
+        native.bind(tuple(at(callback) if f == "nsd_kv_append_layers" else r
+                          for f, r in zip(nsd._BOUND, real)))
+        verify_round(k, v, ks, vs, i32(meta.src_ids, device), i32(meta.dst_ids, device), q,
+                     i32(meta.block_table, device), i32(meta.seq_lens, device),
+                     i32(meta.q_indptr, device), meta.max_q, meta.max_seq_len,
+                     out=torch.zeros_like(q), workspace=ws, window_kv=rows)
+    finally:
+        native.bind(tuple(real))
+    torch.cuda.synchronize()
+    assert seen == [0] and not rows
