@@ -426,7 +426,9 @@ PyObject* py_kv_gather(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return entry([&]() -> PyObject* {
     need(n == 8);
     const Gather g = gather_args(bf16(a[0]), bf16(a[1]), bf16(a[2]), bf16(a[3]), a[4], a[5]);
-    const int32_t l0 = integer(a[6]), nl = a[7] == Py_None ? g.layers - l0 : integer(a[7]);
+    const int32_t l0 = integer(a[6]);
+    need(l0 >= 0);   // (g.layers - l0 cannot overflow; the Python path names the fault)
+    const int32_t nl = a[7] == Py_None ? g.layers - l0 : integer(a[7]);
     void* st = stream_of(any_tensor(a[0]));
     return unlocked([&] { gather(g, l0, nl, st); }, yes, nullptr);
   });

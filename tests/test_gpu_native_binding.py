@@ -139,6 +139,17 @@ def test_draft_small_sample_workspace(device):
     assert torch.equal(call(need), call(4 * need))
 
 
+@pytest.mark.parametrize("layer0", [-1, -2**31, 3, 2**31 - 1])
+def test_gather_layer_range(device, layer0):
+    cfg, meta, (k, v, ks, vs, q) = setup(device)
+    src, dst = i32(meta.src_ids, device), i32(meta.dst_ids, device)
+    before = k.clone()
+    with pytest.raises(nsd.NsdError):
+        nsd.kv_gather(ks, vs, k, v, src, dst, layer0=layer0)
+    torch.cuda.synchronize()
+    assert torch.equal(k, before)
+
+
 def test_faults_raise_the_same(device):
     cfg, meta, (k, v, ks, vs, q) = setup(device)
     table, lens, qi = (i32(x, device) for x in (meta.block_table, meta.seq_lens, meta.q_indptr))
