@@ -2,6 +2,7 @@
 natively, so the same calls with one go through ctypes; outputs are identical,
 with and without the caller's buffers, and a wrong argument raises the same."""
 import ctypes
+import gc
 
 import numpy as np
 import pytest
@@ -187,6 +188,8 @@ def test_a_list_changed_during_the_call(device):
     at = lambda f: ctypes.cast(f, ctypes.c_void_p).value
     real = [at(getattr(nsd.lib(), f)) for f in nsd._BOUND]
     native = nsd._native()
+    gc.collect()         # tensors of other tests' cycles go now, not inside the callback
+    gc.disable()
     try:
         native.bind(tuple(at(callback) if f == "nsd_kv_append_layers" else r
                           for f, r in zip(nsd._BOUND, real)))
@@ -195,6 +198,7 @@ def test_a_list_changed_during_the_call(device):
                      i32(meta.q_indptr, device), meta.max_q, meta.max_seq_len,
                      out=torch.zeros_like(q), workspace=ws, window_kv=rows)
     finally:
+        gc.enable()
         native.bind(tuple(real))
     torch.cuda.synchronize()
     assert seen == [0] and not rows
