@@ -188,7 +188,8 @@ def test_host_alias_refuses_pageable(device):
 
 
 @pytest.mark.parametrize("fused", [False, True])
-def test_round_with_window_append(device, fused):
+@pytest.mark.parametrize("native", [False, True], ids=["by_call", "native"])
+def test_round_with_window_append(device, fused, native):
     # the pools start with the window slots poisoned; the round appends the window rows
     # (the logical K/V at the window positions) before attention, which must then match
     # the oracle on the logical cache; the committed lengths follow acceptance
@@ -216,6 +217,12 @@ def test_round_with_window_append(device, fused):
     acc_in = make_accept(cfg, meta, device)
     committed = torch.empty(meta.bs, dtype=torch.int32, device=device)
     st = i32(meta.stage_table, device) if fused else None
+    buffers = {}
+    if native:       # the caller's output and workspace: the whole round submitted natively
+        buffers = dict(out=torch.empty_like(lay.q[None], device=device),
+                       workspace=nsd.new_workspace(nsd.verify_attention_workspace_size(
+                           meta.bs, cfg.num_q_heads, cfg.num_kv_heads, cfg.head_dim, meta.max_q,
+                           meta.max_seq_len), device))
     outs, acc, _ = verify_round(
         kp.to(device)[None].contiguous(), vp.to(device)[None].contiguous(),
         ks.to(device)[None].contiguous(), vs.to(device)[None].contiguous(),
@@ -225,7 +232,7 @@ def test_round_with_window_append(device, fused):
         accept=(acc_in.p_target, acc_in.q_draft, acc_in.draft_tokens, acc_in.uniforms,
                 int(meta.depth.max())),
         stage_table=st, window_kv=[(kn.to(device), vn.to(device))], committed=committed,
-        prepare="fused" if fused else "gather")
+        prepare="fused" if fused else "gather", **buffers)
     torch.cuda.synchronize()
     from parity import check_attention
     check_attention(meta, lay, outs[0], range(meta.bs))
