@@ -127,10 +127,12 @@ def test_ragged_batch_of_64(device):
 
 
 @pytest.mark.parametrize("bs", [1, 4, 12])
-def test_small_batches_of_long_requests(device, bs):
+@pytest.mark.parametrize("waves", [None, 1024])
+def test_small_batches_of_long_requests(device, bs, waves):
     """Small batches of verify_8b-shaped requests (32/8 heads, head_dim 128,
-    contexts up to 4096, K = 4): the launch uses only about one wave per 20
-    K/V blocks, and every item is cut into parts that the merge kernel
+    contexts up to 4096, K = 4): the item kernel's chunks and their merge, and
+    (an explicit wave count) the wave split, whose launch uses about one wave
+    per 8 K/V blocks and cuts every item into parts that the merge by item
     combines.  Every request is checked, fused and not."""
     rng = np.random.default_rng(40 + bs)
     lens = rng.integers(1024, 4097, bs)
@@ -140,7 +142,7 @@ def test_small_batches_of_long_requests(device, bs):
                         k_hi=4)
     meta = make_meta(cfg, seq_lens=lens, depth=depth)
     for fused in (False, True):
-        _check_all(cfg, meta, device, fused=fused)
+        _check_all(cfg, meta, device, waves=waves, fused=fused)
 
 
 @pytest.mark.parametrize("fused", [False, True])
@@ -261,7 +263,8 @@ def test_workspace_reuse(device, waves):
         check_attention(meta, lay, o, range(cfg.bs))
 
 
-def test_out_of_range_block_ids_are_invisible(device):
+@pytest.mark.parametrize("waves", [None, 4])     # the item kernel, the wave split
+def test_out_of_range_block_ids_are_invisible(device, waves):
     # a block id past the pool makes its tokens invisible; nothing faults
     cfg = custom_config(seed=31, bs=2, vocab=0, n_arriving=0, ctx_lo=64, ctx_hi=64, k_lo=0, k_hi=0,
                         pool_blocks=None)
@@ -269,9 +272,10 @@ def test_out_of_range_block_ids_are_invisible(device):
     lay = make_layer(cfg, meta, 0, "cpu")
     bt = meta.block_table.copy()
     bt[1, 3] = meta.num_blocks + 1000   # last block of request 1: its 16 tokens vanish
-    out = nsd.verify_attention(lay.q.to(device), lay.k_pool.to(device), lay.v_pool.to(device),
-                               i32(bt, device), i32(meta.seq_lens, device),
-                               i32(meta.q_indptr, device), 1, 64)
+    with nsd.attention_waves(waves):
+        out = nsd.verify_attention(lay.q.to(device), lay.k_pool.to(device),
+                                   lay.v_pool.to(device), i32(bt, device),
+                                   i32(meta.seq_lens, device), i32(meta.q_indptr, device), 1, 64)
     torch.cuda.synchronize()
     check_attention(meta, lay, out, [0])
     # request 1's only query (position 63) lives in the dropped block: it sees tokens 0..47
@@ -284,7 +288,13 @@ def test_out_of_range_block_ids_are_invisible(device):
     assert np.abs(out[1:2].float().cpu().numpy() - ref).max() <= 2e-2
 
 
-def test_fused_out_of_range_ids(device):
+# the item kernel; the wave split storing its tiles in line (4 waves, none spare); the wave
+# split in copy mode (64 waves attend, the other 960 copy the staged blocks)
+FUSED_WAYS = [None, 4, 1024]
+
+
+@pytest.mark.parametrize("waves", FUSED_WAYS)
+def test_fused_out_of_range_ids(device, waves):
     # fused pass: a staging id past the staging pool hides its tokens and leaves the
     # destination unwritten; a destination id past the pool is not written, while its
     # (valid) staged tokens stay visible
@@ -297,9 +307,11 @@ def test_fused_out_of_range_ids(device):
     st[1, 3] = meta.stage_num_blocks + 100   # request 1: tokens 48..63 vanish, block not written
     bt[0, 2] = meta.num_blocks + 5           # request 0: block 2 not written, still attended
     kp, vp = lay.k_pool.to(device), lay.v_pool.to(device)
-    out = nsd.gather_verify_attention(lay.q.to(device), kp, vp, lay.k_stage.to(device),
-                                      lay.v_stage.to(device), i32(bt, device), i32(st, device),
-                                      i32(meta.seq_lens, device), i32(meta.q_indptr, device), 1, 64)
+    with nsd.attention_waves(waves):
+        out = nsd.gather_verify_attention(
+            lay.q.to(device), kp, vp, lay.k_stage.to(device), lay.v_stage.to(device),
+            i32(bt, device), i32(st, device), i32(meta.seq_lens, device),
+            i32(meta.q_indptr, device), 1, 64)
     torch.cuda.synchronize()
     # pool: the pairs that stayed valid are copied, the two dropped blocks keep their bytes
     keep = [(int(meta.stage_table[r, b]), int(meta.block_table[r, b]))
@@ -502,7 +514,8 @@ def test_auto_preparation_both_sides_of_the_threshold(device, bs):
     _check_all(cfg, meta, device, prepare="auto")
 
 
-def test_fused_without_query_rows_still_prepares(device):
+@pytest.mark.parametrize("waves", FUSED_WAYS)
+def test_fused_without_query_rows_still_prepares(device, waves):
     # q_indptr all zero (no query rows): the fused call has nothing to attend,
     # but it still moves the arriving requests' blocks into the pool, as the
     # separate gather does
@@ -513,10 +526,11 @@ def test_fused_without_query_rows_still_prepares(device):
     # one row of q and out (an empty tensor has no address); none is read or written
     q0 = torch.zeros((1, cfg.num_q_heads, cfg.head_dim), dtype=torch.bfloat16, device=device)
     qi = torch.zeros(cfg.bs + 1, dtype=torch.int32, device=device)
-    out = nsd.gather_verify_attention(q0, kp, vp, lay.k_stage.to(device), lay.v_stage.to(device),
-                                      i32(meta.block_table, device),
-                                      i32(meta.stage_table, device), i32(meta.seq_lens, device),
-                                      qi, meta.max_q, meta.max_seq_len)
+    with nsd.attention_waves(waves):
+        nsd.gather_verify_attention(q0, kp, vp, lay.k_stage.to(device), lay.v_stage.to(device),
+                                    i32(meta.block_table, device),
+                                    i32(meta.stage_table, device), i32(meta.seq_lens, device),
+                                    qi, meta.max_q, meta.max_seq_len)
     torch.cuda.synchronize()
     ref_k, ref_v = oracle.gather.kv_gather(u16(lay.k_stage)[None], u16(lay.v_stage)[None],
                                            u16(lay.k_pool)[None], u16(lay.v_pool)[None],
