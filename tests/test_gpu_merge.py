@@ -5,11 +5,21 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2609_29364_amd as nsd
 from workload import custom_config, make_meta, make_layer
-from parity import i32, check_attention
+from parity import i32, u16, check_attention
 
 pytestmark = pytest.mark.gpu
+
+
+def check_pool(meta, lay, kp, vp):
+    """The pool after a fused pass: the arriving requests' blocks, every other byte as it was."""
+    want = oracle.gather.kv_gather(u16(lay.k_stage)[None], u16(lay.v_stage)[None],
+                                   u16(lay.k_pool)[None], u16(lay.v_pool)[None], meta.src_ids,
+                                   meta.dst_ids)
+    for got, ref in zip((kp, vp), want):
+        assert np.array_equal(u16(got)[None], ref)
 
 CASES = [
     # (Hq, Hkv, D, seq_lens, depths, waves)
@@ -34,16 +44,17 @@ def test_merge(device, case, fused):
                      arriving=(np.arange(bs) % 2 == 0) & fused)
     lay = make_layer(cfg, meta, 0, device)
     args = (i32(meta.seq_lens, device), i32(meta.q_indptr, device), meta.max_q, meta.max_seq_len)
+    kp, vp = lay.k_pool.clone(), lay.v_pool.clone()
     with nsd.attention_waves(waves):
         if fused:
             out = nsd.gather_verify_attention(
-                lay.q, lay.k_pool.clone(), lay.v_pool.clone(), lay.k_stage, lay.v_stage,
-                i32(meta.block_table, device), i32(meta.stage_table, device), *args)
+                lay.q, kp, vp, lay.k_stage, lay.v_stage, i32(meta.block_table, device),
+                i32(meta.stage_table, device), *args)
         else:
-            out = nsd.verify_attention(lay.q, lay.k_pool, lay.v_pool,
-                                       i32(meta.block_table, device), *args)
+            out = nsd.verify_attention(lay.q, kp, vp, i32(meta.block_table, device), *args)
     torch.cuda.synchronize()
     check_attention(meta, lay, out, range(bs))
+    check_pool(meta, lay, kp, vp)
 
 
 SKEWED = [
@@ -78,3 +89,39 @@ def test_merge_skewed(device, case, fused):
         out = nsd.verify_attention(lay.q, kp, vp, i32(meta.block_table, device), *args)
     torch.cuda.synchronize()
     check_attention(meta, lay, out, range(bs))
+    check_pool(meta, lay, kp, vp)
+
+
+COPY_MODE = [
+    # (Hq, Hkv, D, K, waves, declared longest context or None): 64 of 1024 waves attend, the
+    # others copy the staged blocks (their bytes per wave are below 0.4 of the attention's)
+    (8, 2, 128, 3, 1024, None),
+    (4, 2, 64, 4, 1024, None),
+    (8, 2, 128, 3, None, 81920),     # the wave split by a long declared context
+    (16, 2, 128, 7, None, 20480),    # 64 rows
+]
+
+
+@pytest.mark.parametrize("case", range(len(COPY_MODE)))
+@pytest.mark.parametrize("arriving", ["some", "all"])
+def test_copy_mode(device, case, arriving):
+    hq, hkv, d, k, waves, declared = COPY_MODE[case]
+    lens = [40, 300, 17, 129]
+    cfg = custom_config(seed=970 + case, bs=4, num_q_heads=hq, num_kv_heads=hkv, head_dim=d,
+                        vocab=0, n_arriving=0, pool_blocks=40, staging_order="shuffled")
+    meta = make_meta(cfg, seq_lens=lens, depth=[k] * 4,
+                     arriving=[True, arriving == "all", True, arriving == "all"])
+    lay = make_layer(cfg, meta, 0, device)
+    table, stage = meta.block_table, meta.stage_table
+    if declared:
+        pad = ((0, 0), (0, declared // 16 - table.shape[1]))
+        table, stage = (np.pad(t, pad, constant_values=-1) for t in (table, stage))
+    kp, vp = lay.k_pool.clone(), lay.v_pool.clone()
+    with nsd.attention_waves(waves):
+        out = nsd.gather_verify_attention(
+            lay.q, kp, vp, lay.k_stage, lay.v_stage, i32(table, device), i32(stage, device),
+            i32(meta.seq_lens, device), i32(meta.q_indptr, device), meta.max_q,
+            declared or meta.max_seq_len)
+    torch.cuda.synchronize()
+    check_attention(meta, lay, out, range(4))
+    check_pool(meta, lay, kp, vp)
