@@ -144,14 +144,14 @@ __device__ inline bool request_rows(const Args& A, int r, int& a, int& k) {
   return a < total;
 }
 
-// Request r's first row a and clamped proposal count k; wave 0 evaluates the
-// acceptance tests and leaves the first rejection n in *s_n.  Returns false
-// when the request has no row (nothing to test or draw).
 // Sample row r's uniform: [steps][requests].
 __device__ inline int sample_uniform(const Args& A, int r) {
   return r % A.steps * (A.rows / A.steps) + r / A.steps;
 }
 
+// Request r's first row a and clamped proposal count k; wave 0 evaluates the
+// acceptance tests and leaves the first rejection n in *s_n.  Returns false
+// when the request has no row (nothing to test or draw).
 template <bool SAMPLE>
 __device__ inline bool acceptance(const Args& A, int r, int lane, int wave, int& a, int& k,
                                   int* s_n, int& x_lane) {
