@@ -37,7 +37,8 @@ def test_append_matches_oracle(device, cfg):
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
-def test_append_edges_match_oracle(device, head_dim):
+@pytest.mark.parametrize("shift", [0, 1])       # elements the rows lie past an aligned address
+def test_append_edges_match_oracle(device, head_dim, shift):
     """Windows that cross a block boundary or span three blocks, block ids out
     of range inside a window, positions past the table and contexts shorter
     than the window.  The expected pools are the oracle's append applied token
@@ -69,8 +70,13 @@ def test_append_edges_match_oracle(device, head_dim):
     vn = torch.from_numpy(rng.integers(-30000, 30000, size=(tq, hkv, head_dim),
                                        dtype=np.int16)).view(torch.bfloat16)
     kp, vp = kp0.to(device), vp0.to(device)
-    nsd.kv_append(kp, vp, kn.to(device), vn.to(device), i32(bt, device), i32(sl, device),
-                  i32(qi, device))
+
+    def place(t):
+        flat = torch.empty(t.numel() + shift, dtype=t.dtype, device=device)
+        flat[shift:] = t.flatten().to(device)
+        return flat[shift:].view(t.shape)
+
+    nsd.kv_append(kp, vp, place(kn), place(vn), i32(bt, device), i32(sl, device), i32(qi, device))
     torch.cuda.synchronize()
     rk, rv = u16(kp0), u16(vp0)
     for r, (L, nq, row) in enumerate(cases):
