@@ -1549,75 +1549,77 @@ __global__ __launch_bounds__(1024) void combine_kernel(Params p) {
   }
   if (total_q <= 0 || nq <= 0 || rb <= ra) return;   // nothing attended, or one part holds it all
   const int rows = p.group * nq;
-  const int m0 = (ITEM ? (int)blockIdx.y : wave) * kRows;
-  if (m0 >= rows) return;                // (uniform over the workgroup when ITEM)
   const int split = ITEM ? waves : 1, s0 = ITEM ? wave : 0;
-  const int m = m0 + lane / kLanes, c = lane % kLanes;
-  const int mld = min(m, rows - 1);      // loads clamped into the item's rows
-  MergeAcc acc;
-  merge_init(acc);
-  constexpr int kAhead = kMergeAhead;
-  for (int64_t q0 = ra + s0; q0 <= rb; q0 += (int64_t)split * kAhead) {
-    float2 ml[kAhead];
-    u32x4 w[kAhead];
+  // (ITEM: one row group, uniform over the workgroup)
+  for (int m0 = (ITEM ? (int)blockIdx.y : wave) * kRows; m0 < rows;
+       m0 += ITEM ? rows : waves * kRows) {
+    const int m = m0 + lane / kLanes, c = lane % kLanes;
+    const int mld = min(m, rows - 1);      // loads clamped into the item's rows
+    MergeAcc acc;
+    merge_init(acc);
+    constexpr int kAhead = kMergeAhead;
+    for (int64_t q0 = ra + s0; q0 <= rb; q0 += (int64_t)split * kAhead) {
+      float2 ml[kAhead];
+      u32x4 w[kAhead];
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const int64_t q = min(rb, q0 + (int64_t)u * split);
-      const int64_t slot = MODE == kByChunk ? slot0 + q : 2 * (qoff + q) + (q > ra ? 0 : 1);
-      const int64_t row = slot * (MT * 16) + mld;
-      ml[u] = p.part_ml[row];
-      w[u] = *(const u32x4*)(p.part_o + row * D + c * 8);
-    }
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const int64_t q = q0 + (int64_t)u * split;
-      if (q > rb) continue;
-      if (MODE != kByChunk && sparse) {
-        const Ranges R(T, W, p.w_even, w_odd);
-        if (R.begin(q) >= R.end(q)) continue;
+      for (int u = 0; u < kAhead; ++u) {
+        const int64_t q = min(rb, q0 + (int64_t)u * split);
+        const int64_t slot = MODE == kByChunk ? slot0 + q : 2 * (qoff + q) + (q > ra ? 0 : 1);
+        const int64_t row = slot * (MT * 16) + mld;
+        ml[u] = p.part_ml[row];
+        w[u] = *(const u32x4*)(p.part_o + row * D + c * 8);
       }
-      // bf16 to fp32 by placing each half in the high bits (exact)
-      float o[8];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        o[2 * i] = __uint_as_float(w[u][i] << 16);
-        o[2 * i + 1] = __uint_as_float(w[u][i] & 0xffff0000u);
+      for (int u = 0; u < kAhead; ++u) {
+        const int64_t q = q0 + (int64_t)u * split;
+        if (q > rb) continue;
+        if (MODE != kByChunk && sparse) {
+          const Ranges R(T, W, p.w_even, w_odd);
+          if (R.begin(q) >= R.end(q)) continue;
+        }
+        // bf16 to fp32 by placing each half in the high bits (exact)
+        float o[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          o[2 * i] = __uint_as_float(w[u][i] << 16);
+          o[2 * i + 1] = __uint_as_float(w[u][i] & 0xffff0000u);
+        }
+        merge_into(acc, ml[u].x, ml[u].y, ml[u].y, o);   // the part's rows are O / sum
       }
-      merge_into(acc, ml[u].x, ml[u].y, ml[u].y, o);   // the part's rows are O / sum
     }
-  }
-  if constexpr (ITEM) {
-    // the waves' merges meet in LDS, in wave order
-    extern __shared__ float s_part[];      // [waves][10][64]
-    const int used = (int)min((int64_t)waves, rb - ra + 1);   // (the other waves had no part)
-    if (wave < used) {
-      float* mine = s_part + wave * 640 + lane;
+    if constexpr (ITEM) {
+      // the waves' merges meet in LDS, in wave order
+      extern __shared__ float s_part[];      // [waves][10][64]
+      const int used = (int)min((int64_t)waves, rb - ra + 1);   // (the other waves had no part)
+      if (wave < used) {
+        float* mine = s_part + wave * 640 + lane;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) mine[i * 64] = acc.o[i];
-      mine[512] = acc.m;
-      mine[576] = acc.l;
+        for (int i = 0; i < 8; ++i) mine[i * 64] = acc.o[i];
+        mine[512] = acc.m;
+        mine[576] = acc.l;
+      }
+      __syncthreads();
+      if (wave != 0) return;
+      for (int k = 1; k < used; ++k) {
+        const float* from = s_part + k * 640 + lane;
+        float o[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] = from[i * 64];
+        merge_into(acc, from[512], from[576], 1.f, o);
+      }
     }
-    __syncthreads();
-    if (wave != 0) return;
-    for (int k = 1; k < used; ++k) {
-      const float* from = s_part + k * 640 + lane;
-      float o[8];
+    if (m >= rows) continue;
+    const float inv = acc.l > 0.f ? 1.f / acc.l : 0.f;
+    const int j = m / p.group;
+    const int h = g * p.group + m % p.group;
+    u32x4 w;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) o[i] = from[i * 64];
-      merge_into(acc, from[512], from[576], 1.f, o);
+    for (int i = 0; i < 4; ++i) {
+      const bf16x2 v = {(__bf16)(acc.o[2 * i] * inv), (__bf16)(acc.o[2 * i + 1] * inv)};
+      w[i] = __builtin_bit_cast(uint32_t, v);
     }
+    *(u32x4*)(p.out + ((int64_t)(qo + j) * p.num_q_heads + h) * D + c * 8) = w;
   }
-  if (m >= rows) return;
-  const float inv = acc.l > 0.f ? 1.f / acc.l : 0.f;
-  const int j = m / p.group;
-  const int h = g * p.group + m % p.group;
-  u32x4 w;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const bf16x2 v = {(__bf16)(acc.o[2 * i] * inv), (__bf16)(acc.o[2 * i + 1] * inv)};
-    w[i] = __builtin_bit_cast(uint32_t, v);
-  }
-  *(u32x4*)(p.out + ((int64_t)(qo + j) * p.num_q_heads + h) * D + c * 8) = w;
 }
 
 template <int D, int MT, bool FUSE>
@@ -1762,18 +1764,22 @@ int row_groups(const Params& p) {
   return (p.group * p.max_q + 64 / (D / 8) - 1) / (64 / (D / 8));
 }
 
-// The merge by item, with about one wave for every two of an item's parts, but no
-// more than four rounds of loads for the item of most parts, the longest context
-// (32768 tokens among 16-64, 256 items of head_dim 64: 104 us with the waves the
-// mean item needs, 39 so).
+// The merge by item, with about one wave for every two of an item's parts, and up
+// to four rounds of loads for the item of most parts, the longest context, while
+// all the waves stay within two rounds of the device's (32768 tokens among 16-64,
+// 256 items of head_dim 64: 104 us with the waves the mean item needs, 39 so;
+// without the bound 256 items of 64 rows, one of 32768 among 4096-8192, 172 -> 205).
 template <int D, int MT, int MODE>
 void launch_merge(const Params& p, uint32_t items, int parts, int most_parts,
                   hipStream_t stream) {
+  const int groups = row_groups<D>(p);
+  const int64_t spare = 32 * (int64_t)p.split_groups;   // (split_groups is twice the CUs)
   int split = 1;
   while (split < kMergeMaxSplit &&
-         (2 * split < parts || 4 * kMergeAhead * split < most_parts))
+         (2 * split < parts || (4 * kMergeAhead * split < most_parts &&
+                                2 * split * (int64_t)groups * items <= spare)))
     split *= 2;
-  hipLaunchKernelGGL((combine_kernel<D, MT, MODE>), dim3(items, row_groups<D>(p)),
+  hipLaunchKernelGGL((combine_kernel<D, MT, MODE>), dim3(items, groups),
                      dim3(64 * split), (size_t)split * 640 * sizeof(float), stream, p);
 }
 
@@ -1801,8 +1807,11 @@ void launch(const Params& p, int bs, size_t lds_bytes, hipStream_t stream) {
         (int)std::min<int64_t>(p.merge_waves / p.num_kv_heads, blocks / (FUSE ? 6 : 8));
     launch_merge<D, MT, kByItem>(p, items, (int)(ranges / items), most_parts, stream);
   } else {
+    // a wave per row group, or per two where they are many (2048 items of 64 rows,
+    // one of 1024 tokens among 128-256: 87.5 us with 16 waves, 85.4 with 8)
+    const int groups = row_groups<D>(p);
     hipLaunchKernelGGL((combine_kernel<D, MT, kByRange>), dim3(ranges),
-                       dim3(64 * row_groups<D>(p)), 0, stream, p);
+                       dim3(64 * (groups > 8 ? (groups + 1) / 2 : groups)), 0, stream, p);
   }
 }
 
