@@ -34,8 +34,9 @@ constexpr bool two_waves_per_simd(int columns) { return columns <= 384; }
 //     31 -> 26, 1 of 192 x 8192 31 -> 43;
 //     past one item per CU 8 of 512 x 1536 45 -> 24, but 8 of 400 x 2048 among
 //     256-512 44 -> 50 (although 512 x 2048 is 67 -> 61), with one 16-row tile (16/1
-//     heads, K = 0) 64 of 512 x 2048 41 -> 46, 64 of 512 x 1024 36 -> 26; D 64: 32 of 512 x 3072
-//     30 -> 35, 64 of 1024 x 2048 34 -> 38, 64 of 1024 x 1536 32 -> 29;
+//     heads, K = 0) 64 of 512 x 2048 41 -> 46 and (16/8) 8 of 400 x 1536 among 256-512
+//     35 -> 38, 64 of 512 x 1024 36 -> 26; D 64: 32 of 512 x 3072 30 -> 35, 64 of 1024 x
+//     2048 34 -> 38, 64 of 1024 x 1536 32 -> 29;
 //   items per CU, read only: one tile of D 128 16384 x 128 147 -> 124, 8192 x 512
 //     236 -> 230, 1 of 16384 x 128 90 -> 86; two tiles of D 64 16384 x 512 293 ->
 //     256; two of D 128 1 of 2048 x 256 33 -> 30, 1 of 8192 x 256 68 -> 83; three of
