@@ -1301,8 +1301,8 @@ __device__ inline void item_spans(const Params& p, const int32_t* __restrict__ b
 
 // item_spans with the row tiles the item has, of the MT a batch may have: the
 // batch's deepest request sets MT, and a step's products, softmax and rescale
-// grow with the tiles (24 requests of 1-8 proposals, 8 to 36 rows, 56.1 -> 53.7
-// us; a batch of one depth is unchanged).
+// grow with the tiles (whole items of 24 requests of 1000-4000 tokens and 1-8
+// proposals, 8 to 36 rows, 56.1 -> 53.7 us; a batch of one depth is unchanged).
 template <int D, int MT, int M, bool ARR>
 __device__ __attribute__((always_inline)) inline void item_tiles(
     const Params& p, const int32_t* __restrict__ block_table,
@@ -1473,8 +1473,8 @@ constexpr int kMergeAhead = 4;       // parts a wave loads before it merges the 
 // row group); its waves take the item's parts in turn and their merges meet in
 // LDS, so an item's parts are read in parallel and its row groups go to
 // different CUs.  kByRange: one workgroup per range (of each segment), a wave
-// per row group: it finishes the item the range cuts at its end, if that item
-// began in the range, from the range's record.  Latency is the bound of all:
+// per row group or two: it finishes the item the range cuts at its end, if that
+// item began in the range, from the range's record.  Latency is the bound of all:
 // the launch, one round of loads that says which item it is, one that brings
 // the parts.  Against one workgroup per range that walked an item's parts two
 // at a time: the fused pass of 32 requests (1024-4096 tokens) 12.5 -> 6.2 us
