@@ -1478,8 +1478,8 @@ constexpr int kMergeAhead = 4;       // parts a wave loads before it merges the 
 // the launch, one round of loads that says which item it is, one that brings
 // the parts.  Against one workgroup per range that walked an item's parts two
 // at a time: the fused pass of 32 requests (1024-4096 tokens) 12.5 -> 6.2 us
-// by item, the fused verify_8b pass 11.9 -> 11.4 us and the 512-request decode
-// 6.4 -> 5.4 us by range.
+// by item, the fused verify_8b pass 11.9 -> 10.5 us and the 512-request decode
+// 6.4 -> 4.6 us by range.
 enum MergeMode { kByChunk, kByItem, kByRange };
 
 template <int D, int MT, int MODE>
