@@ -76,10 +76,14 @@ extern "C" nsd_status nsd_kv_gather(const void* src_k, const void* src_v, int64_
   const int64_t block_bytes = (int64_t)num_kv_heads * block_size * head_dim * 2;
   const int32_t vec = (int32_t)(block_bytes / 16);
   clear_stale_error();
-  dim3 grid((uint32_t)n_pairs, (uint32_t)(2 * n_layers));
-  hipLaunchKernelGGL(kv_gather_kernel, grid, dim3(kThreads), 0, (hipStream_t)stream,
-                     (const u32x4*)src_k, (const u32x4*)src_v, src_num_blocks,
-                     (u32x4*)dst_k, (u32x4*)dst_v, dst_num_blocks, src_ids, dst_ids, n_pairs,
-                     layer0, n_layers, vec);
+  // (a launch takes fewer than 2^32 threads in a dimension)
+  constexpr int64_t kPairs = 1 << 23;
+  for (int64_t at = 0; at < n_pairs; at += kPairs) {
+    const int64_t n = n_pairs - at < kPairs ? n_pairs - at : kPairs;
+    hipLaunchKernelGGL(kv_gather_kernel, dim3((uint32_t)n, (uint32_t)(2 * n_layers)),
+                       dim3(kThreads), 0, (hipStream_t)stream, (const u32x4*)src_k,
+                       (const u32x4*)src_v, src_num_blocks, (u32x4*)dst_k, (u32x4*)dst_v,
+                       dst_num_blocks, src_ids + at, dst_ids + at, n, layer0, n_layers, vec);
+  }
   return check_launch("kv_gather");
 }

@@ -201,6 +201,27 @@ def test_gather_empty_plan_and_idempotence(device):
     assert np.array_equal(u16(kp), once)
 
 
+def test_gather_of_more_pairs_than_a_launch_takes(device):
+    # a workgroup of 256 threads per pair: 2^24 pairs and more take several launches
+    n, blocks = (1 << 24) + 5, 40
+    g = torch.Generator(device=device).manual_seed(3)
+    planes = lambda: (torch.randn((blocks, 1, 8, 16, 8), generator=g, device=device).bfloat16(),
+                      torch.randn((blocks, 1, 64, 16), generator=g, device=device).bfloat16())
+    (ks, vs), (kd, vd) = planes(), planes()
+    # every pair but the first and the last ones is out of range (and skipped)
+    src = torch.full((n,), -1, dtype=torch.int32, device=device)
+    pairs = torch.tensor([[0, 3, 7], [5, 9, 1], [n - 1, n - 2, 1 << 24]], device=device)
+    src[pairs[1]], src[pairs[2]] = pairs[0].int() + 10, pairs[0].int() + 20
+    dst = torch.zeros_like(src)
+    dst[pairs[1]], dst[pairs[2]] = pairs[0].int(), pairs[0].int() + 30
+    want_k, want_v = kd.clone(), vd.clone()
+    for d, s in ((0, 10), (30, 20)):
+        want_k[pairs[0] + d], want_v[pairs[0] + d] = ks[pairs[0] + s], vs[pairs[0] + s]
+    nsd.kv_gather(ks, vs, kd, vd, src, dst)
+    torch.cuda.synchronize()
+    assert torch.equal(kd, want_k) and torch.equal(vd, want_v)
+
+
 def test_attention_deterministic_and_permutation_invariant(device):
     cfg = custom_config(seed=21, bs=6, num_q_heads=32, num_kv_heads=8, head_dim=128, vocab=0,
                         ctx_lo=200, ctx_hi=900, n_arriving=0, pool_blocks=None)
