@@ -31,6 +31,7 @@
 // one 1 KiB chunk per row.
 #include "nsd_internal.h"
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -58,6 +59,7 @@ struct Args {
   const float* u;              // uniforms
   const int32_t* q_indptr;     // [rows + 1] (not SAMPLE)
   int32_t rows;                // requests (not SAMPLE) or sample rows
+  int32_t row0;                // accept_row_kernel: the launch's first row
   int32_t vocab, max_k, nchunk;
   int64_t row_stride;          // SAMPLE: elements between requests' rows
   int32_t out_stride;          // SAMPLE: entries between requests' output tokens
@@ -475,7 +477,7 @@ __global__ __launch_bounds__(kRowThreads) void accept_row_kernel(Args A) {
   __shared__ int s_n;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const int r = blockIdx.x;
+  const int r = A.row0 + blockIdx.x;
   int a, k, x_lane;
   if (!acceptance<SAMPLE>(A, r, lane, wave, a, k, &s_n, x_lane)) {
     if (threadIdx.x == 0) write_length(A, r, 0);
@@ -546,12 +548,17 @@ nsd_status launch(bool sample, Args A, int32_t rows, void* workspace, size_t wor
       A.nchunk <= kOnePassChunks || rows == cus || (int64_t)rows * 8 >= (int64_t)cus * 11;
   clear_stale_error();
   if (one_pass) {
-    if (sample)
-      hipLaunchKernelGGL(accept_row_kernel<true>, dim3(rows), dim3(kRowThreads), 0,
-                         (hipStream_t)stream, A);
-    else
-      hipLaunchKernelGGL(accept_row_kernel<false>, dim3(rows), dim3(kRowThreads), 0,
-                         (hipStream_t)stream, A);
+    // (a launch takes fewer than 2^32 threads)
+    constexpr int32_t kRows = 1 << 23;
+    for (A.row0 = 0; A.row0 < rows; A.row0 += kRows) {
+      const dim3 grid(std::min(kRows, rows - A.row0));
+      if (sample)
+        hipLaunchKernelGGL(accept_row_kernel<true>, grid, dim3(kRowThreads), 0,
+                           (hipStream_t)stream, A);
+      else
+        hipLaunchKernelGGL(accept_row_kernel<false>, grid, dim3(kRowThreads), 0,
+                           (hipStream_t)stream, A);
+    }
   } else if (sample) {
     hipLaunchKernelGGL(row_sums_kernel<true>, g1, dim3(kThreads), 0, (hipStream_t)stream, A);
     hipLaunchKernelGGL(pick_kernel<true>, dim3(rows), dim3(kThreads), 0, (hipStream_t)stream, A);
@@ -590,7 +597,7 @@ static nsd_status spec_accept_impl(const char* fn, const float* p_target, const 
     return fail(NSD_ERR_NULL, "%s: NULL pointer argument", fn);
   if (((uintptr_t)p_target | (uintptr_t)(max_k > 0 ? q_draft : p_target)) & 15)
     return fail(NSD_ERR_SHAPE, "%s: probability rows must be 16-byte aligned", fn);
-  Args A{p_target, q_draft, draft_tokens, uniforms, q_indptr, bs, vocab, max_k, 0,
+  Args A{p_target, q_draft, draft_tokens, uniforms, q_indptr, bs, 0, vocab, max_k, 0,
          (int64_t)vocab, 1, 1, seq_lens, committed, nullptr, nullptr, accepted_len, out_tokens};
   return launch(false, A, bs, workspace, workspace_bytes, stream, fn);
 }
@@ -697,7 +704,7 @@ static nsd_status sample_impl(const char* fn, const float* probs, int64_t row_st
   if (n == 0) return NSD_OK;
   if (!probs || !uniforms || !out_tokens) return fail(NSD_ERR_NULL, "%s: NULL pointer argument", fn);
   if ((uintptr_t)probs & 15) return fail(NSD_ERR_SHAPE, "%s: probs must be 16-byte aligned", fn);
-  Args A{probs, nullptr, nullptr, uniforms, nullptr, n * steps, vocab, 0, 0, row_stride,
+  Args A{probs, nullptr, nullptr, uniforms, nullptr, n * steps, 0, vocab, 0, 0, row_stride,
          out_stride, steps, nullptr, nullptr, nullptr, nullptr, nullptr, out_tokens};
   return launch(true, A, n * steps, workspace, workspace_bytes, stream, fn);
 }

@@ -97,3 +97,20 @@ def test_sample_strided_rows_at_full_vocabulary(device, n):
     tok, u = tok.cpu().numpy(), u.cpu().numpy()
     for i in range(k):
         check_samples(probs[:, i].cpu().numpy(), u[i], tok[:, i])
+
+
+def test_more_rows_than_a_launch_takes(device):
+    # a 256-thread workgroup per row: 2^24 rows and more take several launches
+    n, vocab = (1 << 24) + 9, 4
+    g = torch.Generator(device=device).manual_seed(6)
+    p = torch.randint(0, 4, (n, vocab), generator=g, device=device).float()   # exact sums
+    u = torch.randint(0, 1 << 24, (n,), generator=g, device=device).float() * 2.0 ** -24
+    tok = nsd.sample(p, u)
+    # K = 0: an acceptance without proposals draws from the same rows
+    acc, out = nsd.spec_accept(p, None, None, u,
+                               torch.arange(n + 1, dtype=torch.int32, device=device), 0)
+    torch.cuda.synchronize()
+    c = p.double().cumsum(1)
+    want = (c <= (u.double() * c[:, -1])[:, None]).sum(1).int()
+    want = torch.where(c[:, -1] > 0, want, torch.full_like(want, -1))
+    assert torch.equal(tok, want) and torch.equal(out, want) and not acc.any()
