@@ -345,6 +345,7 @@ nsd_status nsd_kv_append(void* k_pool, void* v_pool, int64_t num_blocks, const v
  * [n_layers][stage_num_blocks][...] through stage_rows (the fused
  * preparation's staging bank; an entry out of range, such as -1, is skipped in
  * either).  stage_rows == NULL or stage_num_blocks == 0: no second bank.
+ * A bank's stacked planes stay below 2^63 bytes (else NSD_ERR_SHAPE).
  * Everything else as in nsd_kv_append.
  *
  * Passage: Section 3, as nsd_kv_append.
